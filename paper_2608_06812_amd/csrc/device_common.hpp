@@ -224,27 +224,33 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
 #define OZFP4_GROUP_M 4
 #endif
 constexpr int kGroupM = OZFP4_GROUP_M;
-__device__ __forceinline__ void tile_coords(int64_t bid, int64_t nblocks, int64_t tiles_m,
+// A grid holds fewer than 2^32 work-items, so every count here is below 2^24
+// and the divisions are 32-bit ones.
+__device__ __forceinline__ void tile_coords(unsigned bid, int64_t nblocks, int64_t tiles_m,
                                             int64_t tiles_n, int* l, int64_t* tm, int64_t* tn) {
-  const int64_t xcd = bid & 7, local = bid >> 3;
-  const int64_t T = tiles_m * tiles_n;
-  int64_t t;
+  const unsigned xcd = bid & 7, local = bid >> 3;
+  const unsigned T = (unsigned)(tiles_m * tiles_n);
+  unsigned t;
   if ((T & 7) == 0) {
-    const int64_t per = T >> 3;
-    *l = (int)(local / per);
-    t = xcd * per + (local - (int64_t)(*l) * per);
+    const unsigned per = T >> 3;
+    const unsigned li = local / per;
+    *l = (int)li;
+    t = xcd * per + (local - li * per);
   } else {
-    const int64_t base = nblocks >> 3, rem = nblocks & 7;
-    const int64_t logical = xcd * base + min(xcd, rem) + local;
-    *l = (int)(logical / T);
-    t = logical - (int64_t)(*l) * T;
+    const unsigned base = (unsigned)nblocks >> 3, rem = (unsigned)nblocks & 7;
+    const unsigned logical = xcd * base + min(xcd, rem) + local;
+    const unsigned li = logical / T;
+    *l = (int)li;
+    t = logical - li * T;
   }
-  const int64_t group = t / (kGroupM * tiles_n);
-  const int64_t first = group * kGroupM;
-  const int64_t gm = min(tiles_m - first, (int64_t)kGroupM);
-  const int64_t in = t - group * kGroupM * tiles_n;
-  *tm = first + in % gm;
-  *tn = in / gm;
+  const unsigned span = kGroupM * (unsigned)tiles_n;
+  const unsigned group = t / span;
+  const unsigned first = group * kGroupM;
+  const unsigned gm = min((unsigned)tiles_m - first, (unsigned)kGroupM);
+  const unsigned in = t - group * span;
+  const unsigned col = in / gm;
+  *tm = first + (in - col * gm);
+  *tn = col;
 }
 
 __device__ __forceinline__ v16f mfma_fp4(v4i a, v4i b, v16f c) {
@@ -346,6 +352,101 @@ __device__ __forceinline__ void store_residues(const v16f (&acc)[3][2][2], int l
         *reinterpret_cast<uint32_t*>(Rl + col * ldr + row) = word;
       }
     }
+}
+
+// Residue composition in FP32. The accumulators hold exact multiples of 1/4
+// and every limb of the two-limb splits is within +-8, so with
+// t = acc0 + 13 acc1 + 169 acc2 (in units of 1/4, r = 4 t mod m):
+//   kLevel 1, k <= 1337: |4 t| <= (64 + 13 * 128 + 169 * 64) k < 2^24, so t
+//     is exact, and one reduction t - rint(t 4/m) m/4 (exact FMA) brings it
+//     into (-m/4, m/4);
+//   kLevel 2, k <= 17476: |4 (acc1 + 13 acc2)| <= 960 k < 2^24 is reduced
+//     first, then 13 times that plus acc0;
+//   kLevel 3, larger k: the FP64 composition.
+// rint(t fl(4/m)) is within 2^24 / m * 2^-23 < 0.2 of t 4/m, so a reduced
+// value is within 0.7 m/4, and adding m/4 to a negative one gives [0, m/4).
+// Nine (twelve) full-rate operations an element in place of about twenty
+// FP64 ones and conversions.
+__device__ __forceinline__ int residue_level(int64_t k_pad) {
+  return k_pad <= 1337 ? 1 : (k_pad <= 17476 ? 2 : 3);
+}
+
+__device__ __forceinline__ float reduce_quarter(float t, float inv4, float m4) {
+  return __builtin_fmaf(-__builtin_rintf(t * inv4), m4, t);
+}
+
+// residue bytes of rows 8 g + 4 (lane / 32) .. + 3 of the 32 x 32 tile (i, j)
+template <int kLevel, bool kSkipA1B1>
+__device__ __forceinline__ uint32_t residue_word(const v16f (&acc)[3][2][2], int i, int j, int g,
+                                                 int m, float inv4, float m4, double inv,
+                                                 double md) {
+  uint32_t word = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int v = g * 4 + e;
+    if constexpr (kLevel < 3) {
+      float t = acc[1][i][j][v];
+      if constexpr (!kSkipA1B1) t = __builtin_fmaf(13.0f, acc[2][i][j][v], t);
+      if constexpr (kLevel == 2) t = reduce_quarter(t, inv4, m4);
+      t = __builtin_fmaf(13.0f, t, acc[0][i][j][v]);
+      t = reduce_quarter(t, inv4, m4);
+      // for t < 0 the bit pattern of t (as unsigned) exceeds that of
+      // t + m/4, for t >= 0 it is the smaller one
+      const uint32_t r = min((uint32_t)__float_as_uint(t), (uint32_t)__float_as_uint(t + m4));
+      word = __builtin_amdgcn_cvt_pk_u8_f32(4.0f * __uint_as_float(r), e, word);
+    } else {
+      double d = __builtin_fma(52.0, (double)acc[1][i][j][v], 4.0 * (double)acc[0][i][j][v]);
+      if constexpr (!kSkipA1B1) d = __builtin_fma(676.0, (double)acc[2][i][j][v], d);
+      int r = (int)__builtin_fma(-__builtin_floor(d * inv), md, d);
+      r += (r < 0) ? m : 0;
+      r -= (r >= m) ? m : 0;
+      word |= (uint32_t)r << (8 * e);
+    }
+  }
+  return word;
+}
+
+// A wave's 64 x 64 residues, rows from row0, columns from col0. A swap of
+// half-waves between the two row blocks leaves each lane 32 consecutive rows
+// of one column, stored as two 16-byte words (instead of eight 4-byte ones,
+// whose 8-byte segments cost L2 four times the write requests).
+template <int kLevel, bool kSkipA1B1>
+__device__ __forceinline__ void store_residues_wave(const v16f (&acc)[3][2][2], int m,
+                                                    uint8_t* __restrict__ Rl, int64_t ldr,
+                                                    int64_t row0, int64_t col0, int lane) {
+  const float m4 = 0.25f * (float)m, inv4 = 4.0f / (float)m;
+  const double md = (double)m, inv = 1.0 / md;
+  uint8_t* dst = Rl + (col0 + (lane & 31)) * ldr + row0 + (lane >> 5) * 32;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    v4i w[2];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const uint32_t w0 = residue_word<kLevel, kSkipA1B1>(acc, 0, j, g, m, inv4, m4, inv, md);
+      const uint32_t w1 = residue_word<kLevel, kSkipA1B1>(acc, 1, j, g, m, inv4, m4, inv, md);
+      // lanes 0-31 keep w0 and get the upper lanes' w0 in place of w1;
+      // lanes 32-63 keep w1 and get the lower lanes' w1 in place of w0
+      const auto s = __builtin_amdgcn_permlane32_swap(w0, w1, false, false);
+      w[g >> 1][2 * (g & 1)] = (int)s[0];
+      w[g >> 1][2 * (g & 1) + 1] = (int)s[1];
+    }
+    v4i* p = reinterpret_cast<v4i*>(dst + (int64_t)j * 32 * ldr);
+    p[0] = w[0];
+    p[1] = w[1];
+  }
+}
+
+template <bool kSkipA1B1>
+__device__ __forceinline__ void store_residues_by_k(const v16f (&acc)[3][2][2], int64_t k_pad,
+                                                    int m, uint8_t* __restrict__ Rl, int64_t ldr,
+                                                    int64_t row0, int64_t col0, int lane) {
+  const int level = residue_level(k_pad);
+  if (level == 1)
+    store_residues_wave<1, kSkipA1B1>(acc, m, Rl, ldr, row0, col0, lane);
+  else if (level == 2)
+    store_residues_wave<2, kSkipA1B1>(acc, m, Rl, ldr, row0, col0, lane);
+  else
+    store_residues_wave<3, kSkipA1B1>(acc, m, Rl, ldr, row0, col0, lane);
 }
 
 // One block tile of modulus l. kSkipA1B1: m = 169 = 13^2, where 169 a1 b1 is

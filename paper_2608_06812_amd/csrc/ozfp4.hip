@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "calibrate.hpp"
+#include "gemm_short.hpp"
 #include "karatsuba.hpp"
 #include "kernels.hpp"
 #include "onelimb.hpp"
@@ -301,6 +302,36 @@ void launch_amax_f64(const double* A, int64_t lda, const double* B, int64_t ldb,
                        reinterpret_cast<unsigned long long*>(amax_b), flag, l0);
 }
 
+// Which residue GEMM: the 256 x 128 tile's block has a CU to itself and pays
+// about 7 us around its stages, the 128 x 128 tile (gemm_short.hip) overlaps
+// them with a second block but moves a third more operand bytes. GEMM stage,
+// us, 256 x 128 against 128 x 128, 18 moduli: 63 / 42 at 1024^3, 916 / 571 at
+// 6000 x 6000 x 384, 2328 / 1966 at 6000 x 6000 x 2048, 1885 / 1759 at 4096^3,
+// 29833 / 27431 at 16384 x 16384 x 4096, 13839 / 13820 and 13792 / 13427 at
+// 8192^3, 6690 / 6699 at 4096 x 4096 x 16384, 107793 / 113244 at 16384^3: the
+// line lies at k = 6144. Under four blocks per CU the smaller tile also
+// leaves fewer CUs idle (69 / 39 at 128 x 128 x 8192).
+bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
+  const int64_t blocks = ((m + kTileM - 1) / kTileM) * ((n + kTileN - 1) / kTileN) * nmod;
+  return k <= 6144 || blocks < 1024;
+}
+
+// The residue GEMM of the nmod two-limb moduli of mc, from their planes pa,
+// pb into their residue planes R (leading dimension m_pad).
+hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int64_t plane_a,
+                           int64_t plane_b, int64_t m, int64_t n, int64_t k, int64_t m_pad,
+                           int64_t n_pad, int64_t kblocks, int nmod, const ModConst* mc) {
+  if (use_short_gemm(m, n, k, nmod))
+    return launch_gemm_short(g_stream, pa, pb, R, m_pad, m_pad * n_pad, plane_a, plane_b, m, n, k,
+                             kblocks, nmod, mc);
+  const int64_t tiles_m = m_pad / kTileM, tiles_n = (n + kTileN - 1) / kTileN;
+  const int64_t nblocks = tiles_m * tiles_n * nmod;
+  hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa, pb,
+                     R, plane_a, plane_b, kblocks, tiles_m, tiles_n, nblocks, m_pad, m_pad * n_pad,
+                     mc);
+  return hipGetLastError();
+}
+
 // Stages of the dgemm pipeline, stopping after `last`:
 // 0 scale, 1 encode A, 2 encode B, 3 residue GEMM, 4 CRT.
 // A, B and C are double, or float when p.f32.
@@ -386,30 +417,26 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
   // heads, the default GEMM covers the two-limb moduli after the heads from
   // their planes and residue planes on (with the list's tail constants),
   // and the heads take the single-product GEMM.
-  const int64_t tiles_m = p.m_pad / kTileM, tiles_n = p.n_pad / kTileN;
   const int Lg = L - p.nh;
-  const int64_t nblocks = tiles_m * tiles_n * Lg;
   const int64_t rplane = p.m_pad * p.n_pad;
   if (p.heads) {
     // the heads first: their short burst of residue writes then lands well
     // before the CRT reads
     HIP_TRY(launch_gemm_one_limb(g_stream, pa, pb, R, p.m_pad, rplane, p.plane_a, p.plane_b,
                                  p.m_pad, p.n_pad, p.kblocks, p.nh, d->lists[p.heads].head));
-    if (Lg > 0) {
-      hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream,
-                         pa + 2 * p.nh * p.plane_a, pb + 2 * p.nh * p.plane_b, R + p.nh * rplane,
-                         p.plane_a, p.plane_b, p.kblocks, tiles_m, tiles_n, nblocks, p.m_pad,
-                         rplane, d->lists[p.heads].tail);
-      HIP_TRY(hipGetLastError());
-    }
+    if (Lg > 0)
+      HIP_TRY(launch_gemm_res(pa + 2 * p.nh * p.plane_a, pb + 2 * p.nh * p.plane_b,
+                              R + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
+                              p.n_pad, p.kblocks, Lg, d->lists[p.heads].tail));
   } else if (p.kar) {
+    const int64_t tiles_m = p.m_pad / kTileM, tiles_n = (p.n + kTileN - 1) / kTileN;
+    const int64_t nblocks = tiles_m * tiles_n * L;
     HIP_TRY(launch_gemm_res_kar((unsigned)nblocks, g_stream, pa, pb, R, p.plane_a, p.plane_b,
                                 p.kblocks, tiles_m, tiles_n, nblocks, p.m_pad, p.m_pad * p.n_pad,
                                 d->d_mod, L));
   } else {
-    hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa,
-                       pb, R, p.plane_a, p.plane_b, p.kblocks, tiles_m, tiles_n, nblocks, p.m_pad,
-                       p.m_pad * p.n_pad, d->d_mod);
+    HIP_TRY(launch_gemm_res(pa, pb, R, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad, p.n_pad,
+                            p.kblocks, L, d->d_mod));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
@@ -640,9 +667,7 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
   record(d, 3);
   // residue sets: A1 B1, A1 B2, A2 B1, A2 B2; with heads, the heads by the
   // single-product GEMM, then the two-limb moduli from their planes on
-  const int64_t tiles_m = p.m_pad / kTileM, tiles_n = p.n_pad / kTileN;
   const int Lg = L - p.nh;
-  const int64_t nblocks = tiles_m * tiles_n * Lg;
   const int64_t rplane = p.m_pad * p.n_pad;
   const size_t pa[4] = {p.off_pa1, p.off_pa1, p.off_pa2, p.off_pa2};
   const size_t pb[4] = {p.off_pb1, p.off_pb2, p.off_pb1, p.off_pb2};
@@ -654,10 +679,9 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
                                    p.plane_a, p.plane_b, p.m_pad, p.n_pad, p.kblocks, p.nh,
                                    d->lists[p.heads].head));
     if (Lg > 0)
-      hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream,
-                         ws + pa[q] + 2 * p.nh * p.plane_a, ws + pb[q] + 2 * p.nh * p.plane_b,
-                         Rq + p.nh * rplane, p.plane_a, p.plane_b, p.kblocks, tiles_m, tiles_n,
-                         nblocks, p.m_pad, rplane, d_tail);
+      HIP_TRY(launch_gemm_res(ws + pa[q] + 2 * p.nh * p.plane_a, ws + pb[q] + 2 * p.nh * p.plane_b,
+                              Rq + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
+                              p.n_pad, p.kblocks, Lg, d_tail));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
