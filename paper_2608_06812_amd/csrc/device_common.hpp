@@ -436,26 +436,56 @@ __device__ __forceinline__ void store_residues_wave(const v16f (&acc)[3][2][2], 
   }
 }
 
-template <bool kSkipA1B1>
+// kMinLevel: the smallest level that is compiled in (a higher one than
+// needed is exact too)
+template <bool kSkipA1B1, int kMinLevel>
 __device__ __forceinline__ void store_residues_by_k(const v16f (&acc)[3][2][2], int64_t k_pad,
                                                     int m, uint8_t* __restrict__ Rl, int64_t ldr,
                                                     int64_t row0, int64_t col0, int lane) {
   const int level = residue_level(k_pad);
-  if (level == 1)
+  if (kMinLevel == 1 && level == 1)
     store_residues_wave<1, kSkipA1B1>(acc, m, Rl, ldr, row0, col0, lane);
-  else if (level == 2)
+  else if (level <= 2)
     store_residues_wave<2, kSkipA1B1>(acc, m, Rl, ldr, row0, col0, lane);
   else
     store_residues_wave<3, kSkipA1B1>(acc, m, Rl, ldr, row0, col0, lane);
 }
 
+// The blocks that one XCD runs together share their operand panels in its L2,
+// which holds about 16 stages of them, so they have to stay in step over
+// their 100 and more stages. With the FP64 epilogue (about 9 us of VALU and
+// of narrow stores through the shared L2) they did; with the FP32 one they
+// drift apart: L2 hit rate 84 -> 40 %, GEMM 108.4 -> 114.9 ms at 16384^3 with
+// 18 moduli. So a block whose first copies are issued waits until the other
+// blocks of its group have come as far: the arrivals on an XCD (block id mod
+// 8) are counted in arrive[xcd], `slots` of them (the XCD's CUs, one block
+// each) form a group, the last group takes what is left. The wait ends after
+// 24 polls in any case (about 20 us; a group stays short where another stream
+// holds CUs). With it: 107.0 ms at 16384^3, 13.57 ms against 13.77 at 8192^3.
+constexpr int kLockstepPolls = 24;
+__device__ __forceinline__ void xcd_lockstep(unsigned* arrive, unsigned nblocks, unsigned slots) {
+  if (threadIdx.x != 0) return;
+  const unsigned xcd = blockIdx.x & 7;
+  const unsigned total = (nblocks >> 3) + (xcd < (nblocks & 7) ? 1u : 0u);
+  unsigned* count = arrive + xcd;
+  const unsigned mine =
+      __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned target = min((mine / slots + 1) * slots, total);
+  for (int poll = 0; poll < kLockstepPolls; ++poll) {
+    if (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) break;
+    __builtin_amdgcn_s_sleep(4);
+  }
+}
+
 // One block tile of modulus l. kSkipA1B1: m = 169 = 13^2, where 169 a1 b1 is
 // 0 mod m (Sec. V-A), so the a1 b1 products are not issued (acc2 stays 0).
+// arrive: the lockstep counters (null: no lockstep).
 template <bool kSkipA1B1>
 __device__ __forceinline__ void gemm_res_tile(
     uint8_t* lds, int l, int64_t tm, int64_t tn, const uint8_t* __restrict__ PA,
     const uint8_t* __restrict__ PB, uint8_t* __restrict__ R, int64_t plane_a, int64_t plane_b,
-    int64_t kblocks, int64_t ldr, int64_t rplane, const ModConst* __restrict__ mc) {
+    int64_t kblocks, int64_t ldr, int64_t rplane, const ModConst* __restrict__ mc,
+    unsigned* arrive, unsigned nblocks, unsigned slots) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -583,6 +613,7 @@ __device__ __forceinline__ void gemm_res_tile(
   for (int j = 0; j < kDmaPerWave; ++j) dma(0, j);
 #pragma unroll
   for (int j = 0; j < kDmaPerWave; ++j) dma(1, j);   // nst >= 2 by padding
+  if (arrive) xcd_lockstep(arrive, nblocks, slots);
   wait_vm_lgkm0<kDmaPerWave>();   // stage 0 landed
   block_sync();
   // k fragment 0 of stage 0, in the order in which a stage reads the next
@@ -605,7 +636,8 @@ __device__ __forceinline__ void gemm_res_tile(
   stage(s, false, true);
   stage(s + 1, false, false);
 
-  store_residues<4, 52, 676>(acc, l, tm, tn, wm, wn, lane, R, ldr, rplane, mc);
+  store_residues_by_k<kSkipA1B1, 2>(acc, kblocks * kFragK, mc->m[l], R + (int64_t)l * rplane, ldr,
+                                    tm * kTileM + wm * 64, tn * kTileN + wn * 64, lane);
 }
 
 }  // namespace ozfp4

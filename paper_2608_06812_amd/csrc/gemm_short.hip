@@ -175,8 +175,8 @@ __device__ __forceinline__ void gemm_short_tile(
     if (s + 1 < nst) stage(Odd{}, s + 1, nst - 2 - s);
   }
 
-  store_residues_by_k<kSkipA1B1>(acc, (int64_t)nst * kFragK, mc->m[l], R + (int64_t)l * rplane, ldr,
-                                 tm * kShortTile + wm * 64, tn * kShortTile + wn * 64, lane);
+  store_residues_by_k<kSkipA1B1, 1>(acc, (int64_t)nst * kFragK, mc->m[l], R + (int64_t)l * rplane,
+                                    ldr, tm * kShortTile + wm * 64, tn * kShortTile + wn * 64, lane);
 }
 
 __global__ __launch_bounds__(kShortWaves * 64, 2) void k_gemm_short(

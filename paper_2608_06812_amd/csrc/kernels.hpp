@@ -140,15 +140,18 @@ __global__ __launch_bounds__(256) void k_encode_s8(
 __global__ __launch_bounds__(512, 1) void k_gemm_res(
     const uint8_t* __restrict__ PA, const uint8_t* __restrict__ PB, uint8_t* __restrict__ R,
     int64_t plane_a, int64_t plane_b, int64_t kblocks, int64_t tiles_m, int64_t tiles_n,
-    int64_t nblocks, int64_t ldr, int64_t rplane, const ModConst* __restrict__ mc) {
+    int64_t nblocks, int64_t ldr, int64_t rplane, const ModConst* __restrict__ mc,
+    unsigned* __restrict__ arrive, unsigned slots) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kRing * kStageBytes];
   int l;
   int64_t tm, tn;
   tile_coords(blockIdx.x, nblocks, tiles_m, tiles_n, &l, &tm, &tn);
   if (mc->m[l] == 169)
-    gemm_res_tile<true>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, ldr, rplane, mc);
+    gemm_res_tile<true>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, ldr, rplane, mc, arrive,
+                        (unsigned)nblocks, slots);
   else
-    gemm_res_tile<false>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, ldr, rplane, mc);
+    gemm_res_tile<false>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, ldr, rplane, mc, arrive,
+                         (unsigned)nblocks, slots);
 }
 
 // INT8 variant (Sec. III): three planes per operand, five accumulators

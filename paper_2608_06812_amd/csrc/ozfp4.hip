@@ -53,6 +53,7 @@ struct DeviceState {
   int* h_flag = nullptr;      // pinned host word for the non-finite flag
   hipEvent_t ev[kMaxStages + 1] = {};
   uint8_t* scratch = nullptr; // this device's address of the scratch array
+  int cus_per_xcd = 1;        // CUs of one of the 8 XCDs
 };
 
 HostTables g_tables;
@@ -137,6 +138,10 @@ int init_device(DeviceState& d, const HostTables* T) {
   }
   HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&d.h_flag), sizeof(int), hipHostMallocDefault));
   for (int i = 0; i <= kMaxStages; ++i) HIP_TRY(hipEventCreate(&d.ev[i]));
+  int dev = 0, cus = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  d.cus_per_xcd = std::max(1, cus / 8);
   // each device holds its own copy of the scratch array: keep its address
   void* sp = nullptr;
   HIP_TRY(hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)));
@@ -316,11 +321,19 @@ bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
   return k <= 6144 || blocks < 1024;
 }
 
+// The 256 bytes at the flag word, zeroed by each call's first kernel, also
+// hold the lockstep counters (eight words) of its up to four residue GEMMs.
+unsigned* lockstep_counters(int* flag, int gemm) {
+  return reinterpret_cast<unsigned*>(flag) + 32 + 8 * gemm;
+}
+
 // The residue GEMM of the nmod two-limb moduli of mc, from their planes pa,
-// pb into their residue planes R (leading dimension m_pad).
+// pb into their residue planes R (leading dimension m_pad). arrive: eight
+// lockstep counters, zero.
 hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int64_t plane_a,
                            int64_t plane_b, int64_t m, int64_t n, int64_t k, int64_t m_pad,
-                           int64_t n_pad, int64_t kblocks, int nmod, const ModConst* mc) {
+                           int64_t n_pad, int64_t kblocks, int nmod, const ModConst* mc,
+                           unsigned* arrive, int cus_per_xcd) {
   if (use_short_gemm(m, n, k, nmod))
     return launch_gemm_short(g_stream, pa, pb, R, m_pad, m_pad * n_pad, plane_a, plane_b, m, n, k,
                              kblocks, nmod, mc);
@@ -328,7 +341,7 @@ hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int
   const int64_t nblocks = tiles_m * tiles_n * nmod;
   hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa, pb,
                      R, plane_a, plane_b, kblocks, tiles_m, tiles_n, nblocks, m_pad, m_pad * n_pad,
-                     mc);
+                     mc, arrive, (unsigned)cus_per_xcd);
   return hipGetLastError();
 }
 
@@ -427,7 +440,8 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
     if (Lg > 0)
       HIP_TRY(launch_gemm_res(pa + 2 * p.nh * p.plane_a, pb + 2 * p.nh * p.plane_b,
                               R + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
-                              p.n_pad, p.kblocks, Lg, d->lists[p.heads].tail));
+                              p.n_pad, p.kblocks, Lg, d->lists[p.heads].tail, lockstep_counters(flag, 0),
+                              d->cus_per_xcd));
   } else if (p.kar) {
     const int64_t tiles_m = p.m_pad / kTileM, tiles_n = (p.n + kTileN - 1) / kTileN;
     const int64_t nblocks = tiles_m * tiles_n * L;
@@ -436,7 +450,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
                                 d->d_mod, L));
   } else {
     HIP_TRY(launch_gemm_res(pa, pb, R, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad, p.n_pad,
-                            p.kblocks, L, d->d_mod));
+                            p.kblocks, L, d->d_mod, lockstep_counters(flag, 0), d->cus_per_xcd));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
@@ -681,7 +695,7 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
     if (Lg > 0)
       HIP_TRY(launch_gemm_res(ws + pa[q] + 2 * p.nh * p.plane_a, ws + pb[q] + 2 * p.nh * p.plane_b,
                               Rq + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
-                              p.n_pad, p.kblocks, Lg, d_tail));
+                              p.n_pad, p.kblocks, Lg, d_tail, lockstep_counters(flag, q), d->cus_per_xcd));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
