@@ -1,6 +1,5 @@
 // Device code shared by the translation units of the library: types,
-// constants, the scale helper, the fused encoder, the residue-GEMM tile and
-// its helpers. Templates and inline functions only, so every translation
+// constants, the scale helpers, the residue-GEMM tile and its helpers. Templates and inline functions only, so every translation
 // unit can include it.
 //
 // Data layout (HBM):
@@ -67,149 +66,21 @@ __device__ __forceinline__ int line_shift(uint64_t amax_bits, int cap) {
   return cap - 1 - e;
 }
 
-// ------------------------------------------------------------ Sec. V-A / VI-B
-// Fused integer conversion, residues for every modulus, two-limb split and
-// E2M1 packing, for FP64 (or FP32, taken exactly as FP64) inputs. One wave per fragment (32 lines x 64 k); lane
-// (line % 32, k half) converts its 32 values once, then for each modulus
-// reduces them, looks the codes up in an LDS table and stores 16 bytes to
-// each plane of that modulus: c0 (plane 2l), c1 (plane 2l + 1) and, in the
-// Karatsuba mode (kKar) for a Karatsuba modulus, c0 + c1 (plane
-// 2L + ksum).
-//   x = round_half_even(X * 2^s), |x| <= 2^53, is exact in FP64 and kept as
-//   E x, E = the table entry size in bytes (2, or 4 in the Karatsuba mode).
-//   For each m, q = floor(E x * fl(1/m) / E) is within one of floor(x / m),
-//   so E r = E x - q E m (exact FMA) has r in [-m, 2m), and r indexes a
-//   table over [-m, 2m) that maps every estimate to the codes of its class.
-//   Adding 2^52 plus the table's byte offset to E r gives a double in
-//   [2^52, 2^53) whose low 32 bits are the LDS byte address of the entry.
-//   kWide (capacity above 53 bits): x = A 2^s is an exact double below
-//   2^63; the same floor step first brings E x down to an exact E d with
-//   |d| < 2^15 (the quotient is within 2^8 of floor(x / m), and the FMA's
-//   result is representable, so exact), and the step above then runs on d.
-//   kSecond (the two-term split): the value encoded is the second term
-//   x2 = round_half_even((A 2^s - x) 2^d2), |x2| <= 2^(d2 - 1); A 2^s - x
-//   is exact (the fraction of A 2^s), and so is its product by 2^d2.
-constexpr int kEncWaves = 4;
-
-template <typename T>
-__device__ __forceinline__ uint32_t lut_lookup(double y) {
-  const uint32_t addr = (uint32_t)__double_as_longlong(y);
-  return *reinterpret_cast<__attribute__((address_space(3))) const T*>((size_t)addr);
-}
-
-template <bool kKar, bool kWide, typename TIn = double, bool kSecond = false>
-__global__ __launch_bounds__(256) void k_encode_dgemm(
-    const TIn* __restrict__ X, int64_t rs, int64_t ks, int64_t lines, int64_t k,
-    const uint64_t* __restrict__ amax, int cap, uint8_t* __restrict__ planes,
-    int64_t plane_bytes, int64_t nfrag, int64_t kblocks, int L,
-    const ModConst* __restrict__ mc, const void* __restrict__ lut, int lut_entries, int d2) {
-  typedef typename std::conditional<kKar, uint32_t, uint16_t>::type Entry;
-  constexpr double kE = (double)sizeof(Entry);
-  extern __shared__ __attribute__((aligned(16))) uint8_t s_raw[];
-  Entry* s_lut = reinterpret_cast<Entry*>(s_raw);
-  const Entry* g_lut = reinterpret_cast<const Entry*>(lut);
-  for (int i = threadIdx.x; i < lut_entries; i += 256) s_lut[i] = g_lut[i];
-  __syncthreads();
-  const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)s_raw;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  for (int64_t f = (int64_t)blockIdx.x * kEncWaves + wave; f < nfrag;
-       f += (int64_t)gridDim.x * kEncWaves) {
-    const int64_t rb = f / kblocks, kb = f - rb * kblocks;
-    const int64_t line = rb * kFragLines + (lane & 31);
-    const int64_t kbase = kb * kFragK + (lane >> 5) * 32;
-    const bool live = line < lines;
-    const int s = live ? line_shift(amax[line], cap) : 0;
-    double xe[32];
-    const TIn* src = X + (live ? line : 0) * rs + kbase * ks;
-    if (live && kbase + 32 <= k && ks == 1 && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-      // the lane's 32 values are contiguous (lines along k, as B's
-      // columns): 16-byte loads
-      constexpr int kPer = 16 / (int)sizeof(TIn);
-      typedef TIn Vec __attribute__((ext_vector_type(kPer)));
-      const Vec* v = reinterpret_cast<const Vec*>(src);
+// Maximum of a line over its nchunk partial maxima (line c * pstride + line).
+__device__ __forceinline__ uint64_t partial_max(const uint64_t* __restrict__ part, int64_t pstride,
+                                                int nchunk, int64_t line) {
+  uint64_t v = 0;
+  for (int c = 0; c < nchunk; c += 8) {   // eight loads in flight, the last chunk's repeated
+    uint64_t w[8];
 #pragma unroll
-      for (int e = 0; e < 32 / kPer; ++e) {
-        const Vec x = v[e];
+    for (int e = 0; e < 8; ++e) w[e] = part[min(c + e, nchunk - 1) * pstride + line];
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) xe[e * kPer + q] = (double)x[q];
-      }
-    } else if (live && kbase + 32 <= k) {
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        xe[e] = (double)*src;
-        src += ks;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        xe[e] = (live && kbase + e < k) ? (double)*src : 0.0;
-        src += ks;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 32; ++e) {
-      const double T = __builtin_ldexp(xe[e], s);
-      double t = __builtin_rint(T);
-      if constexpr (kSecond) t = __builtin_rint(__builtin_ldexp(T - t, d2));
-      // finite inputs give |t| <= 2^53 (2^63 when wide); NaN/Inf (reported
-      // by the scale stage) must not drive the table address out of range
-      xe[e] = (__builtin_fabs(t) <= (kWide ? 0x1p63 : 0x1p53)) ? kE * t : 0.0;
-    }
-    uint8_t* out = planes + f * kFragBytes + lane * 16;
-    for (int l = 0; l < L; ++l) {
-      const int m = mc->m[l];
-      const double inv = mc->inv[l] / kE;
-      const double mE = kE * mc->md[l];
-      const double base =
-          0x1p52 + (double)(lds_base + (uint32_t)kE * (uint32_t)(mc->lut_off[l] + m));
-      uint32_t w0[4], w1[4], w2[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint32_t p[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          const int e = g * 8 + h * 2;
-          double x0 = xe[e], x1 = xe[e + 1];
-          if constexpr (kWide) {
-            x0 = __builtin_fma(-__builtin_floor(x0 * inv), mE, x0);
-            x1 = __builtin_fma(-__builtin_floor(x1 * inv), mE, x1);
-          }
-          const double q0 = __builtin_floor(x0 * inv);
-          const double q1 = __builtin_floor(x1 * inv);
-          const uint32_t E0 = lut_lookup<Entry>(__builtin_fma(-q0, mE, x0) + base);
-          const uint32_t E1 = lut_lookup<Entry>(__builtin_fma(-q1, mE, x1) + base);
-          // byte 0: plane-0 byte, byte 1: plane-1 byte (byte 2: sum plane)
-          p[h] = E0 | (E1 << 4);
-        }
-        if constexpr (!kKar) {
-          const uint32_t u = p[0] | (p[1] << 16), v = p[2] | (p[3] << 16);
-          w0[g] = __builtin_amdgcn_perm(v, u, 0x06040200u);
-          w1[g] = __builtin_amdgcn_perm(v, u, 0x07050301u);
-        } else {
-          const uint32_t t01 = __builtin_amdgcn_perm(p[1], p[0], 0x05010400u);
-          const uint32_t t23 = __builtin_amdgcn_perm(p[3], p[2], 0x05010400u);
-          w0[g] = __builtin_amdgcn_perm(t23, t01, 0x05040100u);
-          w1[g] = __builtin_amdgcn_perm(t23, t01, 0x07060302u);
-          const uint32_t s01 = __builtin_amdgcn_perm(p[1], p[0], 0x00000602u);
-          const uint32_t s23 = __builtin_amdgcn_perm(p[3], p[2], 0x00000602u);
-          w2[g] = __builtin_amdgcn_perm(s23, s01, 0x05040100u);
-        }
-      }
-      const v4i p0 = {(int)w0[0], (int)w0[1], (int)w0[2], (int)w0[3]};
-      const v4i p1 = {(int)w1[0], (int)w1[1], (int)w1[2], (int)w1[3]};
-      *reinterpret_cast<v4i*>(out + (int64_t)(2 * l) * plane_bytes) = p0;
-      *reinterpret_cast<v4i*>(out + (int64_t)(2 * l + 1) * plane_bytes) = p1;
-      if constexpr (kKar) {
-        const int ksum = mc->ksum[l];
-        if (ksum >= 0) {
-          const v4i p2 = {(int)w2[0], (int)w2[1], (int)w2[2], (int)w2[3]};
-          *reinterpret_cast<v4i*>(out + (int64_t)(2 * L + ksum) * plane_bytes) = p2;
-        }
-      }
-    }
+    for (int e = 0; e < 8; ++e) v = max(v, w[e]);
   }
+  return v;
 }
+
+constexpr int kEncWaves = 4;   // waves of an encoder block, one fragment each
 
 // ------------------------------------------------------------ Sec. VI-D
 // Block tile index -> (modulus, tile row, tile column). Consecutive block

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "device_common.hpp"
+#include "encode.hpp"
 #include "karatsuba.hpp"
 
 namespace ozfp4 {
@@ -234,15 +235,11 @@ __global__ __launch_bounds__(512, 1) void k_gemm_res_kar(
     gemm_res_tile<false>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, ldr, rplane, mc, nullptr, 0, 0);
 }
 
-hipError_t launch_encode_kar(bool wide, unsigned grid, size_t lds_bytes, hipStream_t stream,
-                             const double* X, int64_t rs, int64_t ks, int64_t lines, int64_t k,
-                             const uint64_t* amax, int cap, uint8_t* planes, int64_t plane_bytes,
-                             int64_t nfrag, int64_t kblocks, int L, const ModConst* mc,
-                             const void* lut, int lut_entries) {
-  auto kern = wide ? k_encode_dgemm<true, true> : k_encode_dgemm<true, false>;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds_bytes, stream, X, rs, ks, lines, k, amax,
-                     cap, planes, plane_bytes, nfrag, kblocks, L, mc, lut, lut_entries, 0);
-  return hipGetLastError();
+hipError_t launch_encode_kar(hipStream_t stream, const ConvOperand& a, const ConvOperand& b, int L,
+                             const ModConst& mod, const ModConst* mc, const uint32_t* lut) {
+  if (a.cap > 53)
+    return launch_encode_kernel<true, true, double>(stream, a, b, L, mod, mc, lut, 1, 0);
+  return launch_encode_kernel<true, false, double>(stream, a, b, L, mod, mc, lut, 1, 0);
 }
 
 hipError_t launch_gemm_res_kar(unsigned grid, hipStream_t stream, const uint8_t* PA,

@@ -1,5 +1,5 @@
-// gfx950 kernels of the default path: line maxima and shifts, the INT8
-// encoder, the residue GEMM, the INT8 GEMM and the CRT. Included by
+// gfx950 kernels of the default path: the INT8 encoder, the residue GEMM,
+// the INT8 GEMM and the CRT. Included by
 // ozfp4.hip only (the Karatsuba kernels live in karatsuba.hip, a separate
 // translation unit, so that their code cannot change how the compiler
 // schedules these).
@@ -27,68 +27,6 @@ __global__ void k_fill_i32_matrix(int32_t* __restrict__ C, int64_t m, int64_t n,
   const int64_t total = m * n, stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride)
     C[(t % m) + (t / m) * ldc] = 0;
-}
-
-// Row maxima of |X| for lines that are adjacent in memory (X[line + kk*ld]):
-// one thread per line over a chunk of kk, then a 64-bit atomic max of the
-// bit patterns (for non-negative doubles the integer order of the patterns
-// is the numeric order; NaN/Inf patterns sort above every finite value).
-constexpr int kAmaxChunk = 256;
-__global__ __launch_bounds__(256) void k_amax_adjacent_lines(
-    const double* __restrict__ X, int64_t ld, int64_t lines, int64_t k,
-    unsigned long long* __restrict__ amax, int* __restrict__ flag) {
-  int64_t line = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (line >= lines) return;
-  int64_t k0 = (int64_t)blockIdx.y * kAmaxChunk;
-  int64_t k1 = min(k, k0 + kAmaxChunk);
-  const uint64_t* p = reinterpret_cast<const uint64_t*>(X) + line;
-  uint64_t mx = 0;
-  int64_t kk = k0;
-  for (; kk + 4 <= k1; kk += 4) {
-    uint64_t a = p[kk * ld] & kAbsMask, b = p[(kk + 1) * ld] & kAbsMask;
-    uint64_t c = p[(kk + 2) * ld] & kAbsMask, d = p[(kk + 3) * ld] & kAbsMask;
-    mx = max(mx, max(max(a, b), max(c, d)));
-  }
-  for (; kk < k1; ++kk) mx = max(mx, p[kk * ld] & kAbsMask);
-  if (mx >= kNonFinite) *flag = 1;
-  if (mx) atomicMax(&amax[line], (unsigned long long)mx);
-}
-
-// Maxima of |X| for lines contiguous in memory (X[kk + line*ld]): one wave
-// per (line, chunk of 4096 k), a wave-wide max, one atomic per wave.
-constexpr int kAmaxContigChunk = 4096;
-__global__ __launch_bounds__(256) void k_amax_contig_lines(
-    const double* __restrict__ X, int64_t ld, int64_t lines, int64_t k,
-    unsigned long long* __restrict__ amax, int* __restrict__ flag, int64_t line0) {
-  int64_t line = line0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  int lane = threadIdx.x & 63;
-  if (line >= lines) return;
-  int64_t k0 = (int64_t)blockIdx.y * kAmaxContigChunk;
-  int64_t k1 = min(k, k0 + kAmaxContigChunk);
-  const uint64_t* p = reinterpret_cast<const uint64_t*>(X) + line * ld;
-  uint64_t mx = 0;
-  int64_t kk = k0 + lane;
-  for (; kk + 192 < k1; kk += 256) {
-    uint64_t a = p[kk] & kAbsMask, b = p[kk + 64] & kAbsMask;
-    uint64_t c = p[kk + 128] & kAbsMask, d = p[kk + 192] & kAbsMask;
-    mx = max(mx, max(max(a, b), max(c, d)));
-  }
-  for (; kk < k1; kk += 64) mx = max(mx, p[kk] & kAbsMask);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    uint64_t o = __shfl_xor(mx, off, 64);
-    mx = max(mx, o);
-  }
-  if (lane == 0) {
-    if (mx >= kNonFinite) *flag = 1;
-    if (mx) atomicMax(&amax[line], (unsigned long long)mx);
-  }
-}
-
-__global__ void k_shifts(const uint64_t* __restrict__ amax, int64_t lines, int cap,
-                         int32_t* __restrict__ out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < lines) out[i] = line_shift(amax[i], cap);
 }
 
 // INT8 encoder (Sec. III): three greedy limbs per value from a 256-entry

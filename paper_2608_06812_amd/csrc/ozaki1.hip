@@ -58,20 +58,31 @@ constexpr uint32_t kResidueCarries = residue_carries();
 // limb per plane: q = floor(t fl(1/13)) is within one of floor(t / 13), so
 // r = t - 13 q (exact FMA) is corrected into [0, 13) with one step each
 // way; the digit and its code come from r, and t becomes (t - digit) / 13.
-__global__ __launch_bounds__(256) void k_encode_ozi(
-    const double* __restrict__ X, int64_t rs, int64_t ks, int64_t lines, int64_t k,
-    const uint64_t* __restrict__ amax, int cap, uint8_t* __restrict__ planes, int64_t plane_bytes,
-    int64_t nfrag, int64_t kblocks, int nplanes) {
+// Blocks below blocks_a encode operand a, the rest b.
+__global__ __launch_bounds__(256) void k_encode_ozi(ConvOperand a, ConvOperand b,
+                                                    uint32_t blocks_a, int nplanes) {
+  const bool is_b = blockIdx.x >= blocks_a;
+  const uint32_t block = is_b ? blockIdx.x - blocks_a : blockIdx.x;
+  const uint32_t nblocks = is_b ? gridDim.x - blocks_a : blocks_a;
+  const ConvOperand& op = is_b ? b : a;
+  const int64_t rs = op.rs, ks = op.ks, lines = op.lines, k = op.k;
+  const int64_t plane_bytes = op.plane_bytes;
+  const double* X = reinterpret_cast<const double*>(op.X);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const double limit = __builtin_ldexp(1.0, cap);
-  for (int64_t f = (int64_t)blockIdx.x * kEncWaves + wave; f < nfrag;
-       f += (int64_t)gridDim.x * kEncWaves) {
-    const int64_t rb = f / kblocks, kb = f - rb * kblocks;
-    const int64_t line = rb * kFragLines + (lane & 31);
-    const int64_t kbase = kb * kFragK + (lane >> 5) * 32;
+  const double limit = __builtin_ldexp(1.0, op.cap);
+  const uint32_t kfrags = op.kfrags, nfrag = op.blocks * kfrags;
+  for (uint32_t f = block * kEncWaves + wave; f < nfrag; f += nblocks * kEncWaves) {
+    const uint32_t rb = f / kfrags, kb = f - rb * kfrags;
+    const int64_t line = (int64_t)rb * kFragLines + (lane & 31);
+    const int64_t kbase = (int64_t)kb * kFragK + (lane >> 5) * 32;
     const bool live = line < lines;
-    const int s = live ? line_shift(amax[line], cap) : 0;
+    int s = 0;
+    if (live) {
+      const uint64_t mx = partial_max(op.part, op.pstride, op.nchunk, line);
+      s = line_shift(mx, op.cap);
+      if (kb == 0 && lane < 32) op.amax[line] = mx;
+    }
     double t[32];
     const double* src = X + (live ? line : 0) * rs + kbase * ks;
     if (live && kbase + 32 <= k) {
@@ -93,7 +104,7 @@ __global__ __launch_bounds__(256) void k_encode_ozi(
       // NaN/Inf (reported by the scale stage) become 0 so the loop stays bounded
       t[e] = (__builtin_fabs(v) <= limit) ? v : 0.0;
     }
-    uint8_t* out = planes + f * kFragBytes + lane * 16;
+    uint8_t* out = op.planes + ((int64_t)rb * op.kblocks + kb) * kFragBytes + lane * 16;
     for (int p = 0; p < nplanes; ++p) {
       uint32_t w[4];
 #pragma unroll
@@ -333,12 +344,10 @@ __global__ __launch_bounds__(256) void k_ozi_reduce(
 
 // ---------------------------------------------------------------- launches
 
-hipError_t launch_encode_ozi(unsigned grid, hipStream_t stream, const double* X, int64_t rs,
-                             int64_t ks, int64_t lines, int64_t k, const uint64_t* amax, int cap,
-                             uint8_t* planes, int64_t plane_bytes, int64_t nfrag, int64_t kblocks,
+hipError_t launch_encode_ozi(hipStream_t stream, const ConvOperand& a, const ConvOperand& b,
                              int nplanes) {
-  hipLaunchKernelGGL(k_encode_ozi, dim3(grid), dim3(256), 0, stream, X, rs, ks, lines, k, amax,
-                     cap, planes, plane_bytes, nfrag, kblocks, nplanes);
+  const uint32_t ba = encode_blocks(a), bb = encode_blocks(b);
+  hipLaunchKernelGGL(k_encode_ozi, dim3(ba + bb), dim3(256), 0, stream, a, b, ba, nplanes);
   return hipGetLastError();
 }
 

@@ -4,12 +4,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "convert.hpp"
+
 namespace ozfp4 {
 
-// k_encode_ozi: nplanes greedy limb planes of the lines of X
-hipError_t launch_encode_ozi(unsigned grid, hipStream_t stream, const double* X, int64_t rs,
-                             int64_t ks, int64_t lines, int64_t k, const uint64_t* amax, int cap,
-                             uint8_t* planes, int64_t plane_bytes, int64_t nfrag, int64_t kblocks,
+// k_encode_ozi: nplanes greedy limb planes of the lines of both operands
+hipError_t launch_encode_ozi(hipStream_t stream, const ConvOperand& a, const ConvOperand& b,
                              int nplanes);
 
 // k_gemm_ozi over every 128 x 128 tile of every block anti-diagonal; H holds

@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "calibrate.hpp"
+#include "convert.hpp"
 #include "gemm_short.hpp"
 #include "karatsuba.hpp"
 #include "kernels.hpp"
@@ -22,7 +23,7 @@
 using namespace ozfp4;
 
 // Workspace of ozfp4_dgemm_noalloc (limb planes, residues, line maxima and
-// the non-finite flag of one call): a fixed array in every device's copy of
+// the flag words of one call): a fixed array in every device's copy of
 // the code object, so that entry point never allocates. In host code this
 // name is a host-side stand-in, not a device address: kernels and copies
 // take the address hipGetSymbolAddress returns for the current device
@@ -50,7 +51,8 @@ struct DeviceState {
   } lists[kMaxHeads + 1];
   uint8_t* ws = nullptr;
   size_t ws_bytes = 0;
-  int* h_flag = nullptr;      // pinned host word for the non-finite flag
+  int* h_flag = nullptr;      // pinned host word for the non-finite flag,
+  int* h_flag_dev = nullptr;  // and its device address
   hipEvent_t ev[kMaxStages + 1] = {};
   uint8_t* scratch = nullptr; // this device's address of the scratch array
   int cus_per_xcd = 1;        // CUs of one of the 8 XCDs
@@ -136,7 +138,8 @@ int init_device(DeviceState& d, const HostTables* T) {
     HIP_TRY(hipMemcpy(Ld.lut, Lh.lut.data(), Lh.lut.size() * sizeof(uint16_t),
                       hipMemcpyHostToDevice));
   }
-  HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&d.h_flag), sizeof(int), hipHostMallocDefault));
+  HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&d.h_flag), sizeof(int), hipHostMallocCoherent));
+  HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&d.h_flag_dev), d.h_flag, 0));
   for (int i = 0; i <= kMaxStages; ++i) HIP_TRY(hipEventCreate(&d.ev[i]));
   int dev = 0, cus = 0;
   HIP_TRY(hipGetDevice(&dev));
@@ -291,20 +294,69 @@ int encode_grid(int64_t nfrag) {
   return (int)std::min<int64_t>(want, 256 * 16);
 }
 
-// Line maxima of the FP64 operands: rows of A (adjacent in memory) and
-// columns of B (contiguous), one wave per column of B in launches of at
-// most kLaunchThreads threads.
-void launch_amax_f64(const double* A, int64_t lda, const double* B, int64_t ldb, int64_t m,
-                     int64_t n, int64_t k, uint64_t* amax_a, uint64_t* amax_b, int* flag) {
-  hipLaunchKernelGGL(k_amax_adjacent_lines, dim3(blocks_for(m, 256), blocks_for(k, kAmaxChunk)),
-                     dim3(256), 0, g_stream, A, lda, m, k,
-                     reinterpret_cast<unsigned long long*>(amax_a), flag);
-  constexpr int64_t kLines = kLaunchThreads / 64;
-  for (int64_t l0 = 0; l0 < n; l0 += kLines)
-    hipLaunchKernelGGL(k_amax_contig_lines,
-                       dim3(blocks_for(std::min(n - l0, kLines), 4), blocks_for(k, kAmaxContigChunk)),
-                       dim3(256), 0, g_stream, B, ldb, n, k,
-                       reinterpret_cast<unsigned long long*>(amax_b), flag, l0);
+// The flag word of a call about to start, zero: the line-maximum kernel
+// writes host memory directly where a value is NaN or infinite, so the call
+// ends with its last kernel and not with a copy of the flag (a 3.4 us copy
+// kernel and its gap).
+int* start_flag(DeviceState* d) {
+  *static_cast<volatile int*>(d->h_flag) = 0;
+  return d->h_flag_dev;
+}
+
+// One operand of a conversion stage over the padded layout; its partial
+// line maxima go to part.
+ConvOperand conv_operand(const void* X, int64_t rs, int64_t ks, int64_t lines, int64_t k, int cap,
+                         int64_t lines_pad, int64_t kblocks, int64_t plane_bytes, uint8_t* planes,
+                         uint64_t* amax, uint64_t* part) {
+  ConvOperand op = {};
+  op.X = X;
+  op.rs = rs;
+  op.ks = ks;
+  op.lines = lines;
+  op.k = k;
+  op.part = part;
+  op.pstride = lines_pad;
+  op.cap = cap;
+  op.amax = amax;
+  op.planes = planes;
+  op.plane_bytes = plane_bytes;
+  op.kblocks = kblocks;
+  op.blocks = (uint32_t)(lines_pad / kFragLines);
+  op.kfrags = (uint32_t)kblocks;
+  plan_line_max(&op);
+  return op;
+}
+
+// The operands A (m x k) and B (k x n) of a plan, column-major. Their partial
+// maxima lie where the residues (scheme I: the partial sums) will be written
+// after the encoder has read them: (m_pad + n_pad) 8 kMaxChunks bytes at
+// most, and those take at least 512 max(m_pad, n_pad).
+static_assert(2 * 8 * kMaxChunks <= kTile * OZFP4_MIN_MODULI, "partial maxima exceed the residues");
+template <class Plan>
+void conv_operands(const Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb, int cA,
+                   int cB, uint8_t* ws, uint8_t* pa, uint8_t* pb, size_t off_part, ConvOperand* a,
+                   ConvOperand* b) {
+  uint64_t* part = reinterpret_cast<uint64_t*>(ws + off_part);
+  *a = conv_operand(A, 1, lda, p.m, p.k, cA, p.m_pad, p.kblocks, p.plane_a, pa,
+                    reinterpret_cast<uint64_t*>(ws + p.off_amax_a), part);
+  *b = conv_operand(B, ldb, 1, p.n, p.k, cB, p.n_pad, p.kblocks, p.plane_b, pb,
+                    reinterpret_cast<uint64_t*>(ws + p.off_amax_b), part + a->nchunk * p.m_pad);
+}
+
+// A conversion stage's encoder: `launch` takes both operands in one launch;
+// a profiled call gives each its own launch, and so its own stage time.
+template <class Launch>
+hipError_t encode_stages(DeviceState* d, const ConvOperand& a, const ConvOperand& b,
+                         Launch&& launch) {
+  if (!g_profile) return launch(a, b);
+  ConvOperand none = a;
+  none.blocks = 0;
+  hipError_t rc = launch(a, none);
+  record(d, 2);
+  none = b;
+  none.blocks = 0;
+  if (rc == hipSuccess) rc = launch(none, b);
+  return rc;
 }
 
 // Which residue GEMM: the 256 x 128 tile's block has a CU to itself and pays
@@ -321,15 +373,9 @@ bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
   return k <= 6144 || blocks < 1024;
 }
 
-// The 256 bytes at the flag word, zeroed by each call's first kernel, also
-// hold the lockstep counters (eight words) of its up to four residue GEMMs.
-unsigned* lockstep_counters(int* flag, int gemm) {
-  return reinterpret_cast<unsigned*>(flag) + 32 + 8 * gemm;
-}
-
 // The residue GEMM of the nmod two-limb moduli of mc, from their planes pa,
 // pb into their residue planes R (leading dimension m_pad). arrive: eight
-// lockstep counters, zero.
+// lockstep counters.
 hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int64_t plane_a,
                            int64_t plane_b, int64_t m, int64_t n, int64_t k, int64_t m_pad,
                            int64_t n_pad, int64_t kblocks, int nmod, const ModConst* mc,
@@ -339,6 +385,8 @@ hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int
                              kblocks, nmod, mc);
   const int64_t tiles_m = m_pad / kTileM, tiles_n = (n + kTileN - 1) / kTileN;
   const int64_t nblocks = tiles_m * tiles_n * nmod;
+  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, g_stream, reinterpret_cast<uint64_t*>(arrive),
+                     (int64_t)4, (uint64_t)0);
   hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa, pb,
                      R, plane_a, plane_b, kblocks, tiles_m, tiles_n, nblocks, m_pad, m_pad * n_pad,
                      mc, arrive, (unsigned)cus_per_xcd);
@@ -349,80 +397,33 @@ hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int
 // 0 scale, 1 encode A, 2 encode B, 3 residue GEMM, 4 CRT.
 // A, B and C are double, or float when p.f32.
 int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, const void* Bv,
-              int64_t ldb, void* Cv, int64_t ldc, int last, uint8_t* planes_a_out,
+              int64_t ldb, void* Cv, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
               uint8_t* planes_b_out, uint8_t* ws_base = nullptr) {
-  const double* A = static_cast<const double*>(Av);
-  const double* B = static_cast<const double*>(Bv);
-  const float* Af = static_cast<const float*>(Av);
-  const float* Bf = static_cast<const float*>(Bv);
   const HostTables* T = tables();
   uint8_t* ws = ws_base ? ws_base : d->ws;
-  uint64_t* amax_a = reinterpret_cast<uint64_t*>(ws + p.off_amax_a);
-  uint64_t* amax_b = reinterpret_cast<uint64_t*>(ws + p.off_amax_b);
-  int* flag = reinterpret_cast<int*>(ws + p.off_flag);
+  unsigned* arrive = reinterpret_cast<unsigned*>(ws + p.off_flag) + 32;
   uint8_t* pa = planes_a_out ? planes_a_out : ws + p.off_pa;
   uint8_t* pb = planes_b_out ? planes_b_out : ws + p.off_pb;
   uint8_t* R = ws + p.off_r;
   const int L = p.L;
+  ConvOperand a, b;
+  conv_operands(p, Av, lda, Bv, ldb, p.cA, p.cB, ws, pa, pb, p.off_r, &a, &b);
 
   record(d, 0);
-  // stage 0: line maxima (the flag word shares the zero fill)
-  const int64_t nzero = (int64_t)((p.off_flag + 256 - p.off_amax_a) / sizeof(uint64_t));
-  hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(nzero, 256)), dim3(256), 0, g_stream,
-                     amax_a, nzero, (uint64_t)0);
-  if (p.f32) {
-    HIP_TRY(launch_amax_f32(g_stream, Af, lda, Bf, ldb, p.m, p.n, p.k, amax_a, amax_b, flag));
-  } else {
-    launch_amax_f64(A, lda, B, ldb, p.m, p.n, p.k, amax_a, amax_b, flag);
-  }
-  HIP_TRY(hipGetLastError());
+  // stage 0: line maxima
+  HIP_TRY(launch_line_max(g_stream, p.f32, a, b, flag));
   record(d, 1);
   if (last < 1) return OZFP4_OK;
 
-  // stage 1, 2: fused conversion + residues + limbs + E2M1 packing
+  // stage 1, 2: fused conversion + residues + limbs + E2M1 packing; the
+  // Karatsuba mode's encoder lives in its own translation unit
   const ModConst& mod = p.heads ? T->lists[p.heads].mod : T->mod;
   const ModConst* d_mod = p.heads ? d->lists[p.heads].mod : d->d_mod;
-  const int lut_entries = mod.lut_off[L - 1] + 3 * mod.m[L - 1];
-  const size_t lut_bytes = (p.kar ? sizeof(uint32_t) : sizeof(uint16_t)) * (size_t)lut_entries;
-  const void* lut = p.kar ? static_cast<const void*>(d->d_lut_k)
-                          : static_cast<const void*>(p.heads ? d->lists[p.heads].lut : d->d_lut);
-  const int64_t nfa = (p.m_pad / kFragLines) * p.kblocks;
-  const int64_t nfb = (p.n_pad / kFragLines) * p.kblocks;
-  // an operand whose capacity exceeds 53 bits takes the wide encoder; the
-  // Karatsuba mode's encoder lives in its own translation unit
-  if (p.f32) {
-    HIP_TRY(launch_encode_f32((unsigned)encode_grid(nfa), lut_bytes, g_stream, Af, (int64_t)1, lda,
-                              p.m, p.k, amax_a, p.cA, pa, p.plane_a, nfa, p.kblocks, L, d_mod,
-                              lut, lut_entries));
-  } else if (p.kar) {
-    HIP_TRY(launch_encode_kar(p.cA > 53, (unsigned)encode_grid(nfa), lut_bytes, g_stream, A,
-                              (int64_t)1, lda, p.m, p.k, amax_a, p.cA, pa, p.plane_a, nfa,
-                              p.kblocks, L, d->d_mod, lut, lut_entries));
-  } else {
-    auto enc = p.cA > 53 ? k_encode_dgemm<false, true> : k_encode_dgemm<false, false>;
-    hipLaunchKernelGGL(enc,
-                       dim3(encode_grid(nfa)), dim3(256), lut_bytes, g_stream, A, (int64_t)1, lda,
-                       p.m, p.k, amax_a, p.cA, pa, p.plane_a, nfa, p.kblocks, L, d_mod, lut,
-                       lut_entries, 0);
-  }
-  HIP_TRY(hipGetLastError());
-  record(d, 2);
-  if (p.f32) {
-    HIP_TRY(launch_encode_f32((unsigned)encode_grid(nfb), lut_bytes, g_stream, Bf, ldb, (int64_t)1,
-                              p.n, p.k, amax_b, p.cB, pb, p.plane_b, nfb, p.kblocks, L, d_mod,
-                              lut, lut_entries));
-  } else if (p.kar) {
-    HIP_TRY(launch_encode_kar(p.cB > 53, (unsigned)encode_grid(nfb), lut_bytes, g_stream, B, ldb,
-                              (int64_t)1, p.n, p.k, amax_b, p.cB, pb, p.plane_b, nfb, p.kblocks,
-                              L, d->d_mod, lut, lut_entries));
-  } else {
-    auto enc = p.cB > 53 ? k_encode_dgemm<false, true> : k_encode_dgemm<false, false>;
-    hipLaunchKernelGGL(enc,
-                       dim3(encode_grid(nfb)), dim3(256), lut_bytes, g_stream, B, ldb, (int64_t)1,
-                       p.n, p.k, amax_b, p.cB, pb, p.plane_b, nfb, p.kblocks, L, d_mod, lut,
-                       lut_entries, 0);
-  }
-  HIP_TRY(hipGetLastError());
+  const uint16_t* lut = p.heads ? d->lists[p.heads].lut : d->d_lut;
+  HIP_TRY(encode_stages(d, a, b, [&](const ConvOperand& x, const ConvOperand& y) {
+    return p.kar ? launch_encode_kar(g_stream, x, y, L, mod, d_mod, d->d_lut_k)
+                 : launch_encode(g_stream, p.f32, x, y, L, mod, d_mod, lut, 1, 0);
+  }));
   record(d, 3);
   if (last < 3) return OZFP4_OK;
 
@@ -440,7 +441,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
     if (Lg > 0)
       HIP_TRY(launch_gemm_res(pa + 2 * p.nh * p.plane_a, pb + 2 * p.nh * p.plane_b,
                               R + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
-                              p.n_pad, p.kblocks, Lg, d->lists[p.heads].tail, lockstep_counters(flag, 0),
+                              p.n_pad, p.kblocks, Lg, d->lists[p.heads].tail, arrive,
                               d->cus_per_xcd));
   } else if (p.kar) {
     const int64_t tiles_m = p.m_pad / kTileM, tiles_n = (p.n + kTileN - 1) / kTileN;
@@ -450,7 +451,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
                                 d->d_mod, L));
   } else {
     HIP_TRY(launch_gemm_res(pa, pb, R, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad, p.n_pad,
-                            p.kblocks, L, d->d_mod, lockstep_counters(flag, 0), d->cus_per_xcd));
+                            p.kblocks, L, d->d_mod, arrive, d->cus_per_xcd));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
@@ -462,7 +463,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
   const int nc = (p.heads ? T->lists[p.heads].crt : T->crt)[L].nc;
   if (p.f32) {
     HIP_TRY(launch_crt_f32(g_stream, nc, R, p.m_pad, rplane, p.m, p.n,
-                           amax_a, amax_b, p.cA, p.cB, crt, static_cast<float*>(Cv),
+                           a.amax, b.amax, p.cA, p.cB, crt, static_cast<float*>(Cv),
                            ldc));
     record(d, 5);
     return OZFP4_OK;
@@ -472,11 +473,11 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
     const unsigned grid = blocks_for(std::min(nthreads - t0, kLaunchThreads), 256);
     if (nc == 3)
       hipLaunchKernelGGL(k_crt<3>, dim3(grid), dim3(256), 0, g_stream, R, p.m_pad,
-                         rplane, p.m, p.n, amax_a, amax_b, p.cA, p.cB, crt, C,
+                         rplane, p.m, p.n, a.amax, b.amax, p.cA, p.cB, crt, C,
                          ldc, t0);
     else
       hipLaunchKernelGGL(k_crt<4>, dim3(grid), dim3(256), 0, g_stream, R, p.m_pad,
-                         rplane, p.m, p.n, amax_a, amax_b, p.cA, p.cB, crt, C,
+                         rplane, p.m, p.n, a.amax, b.amax, p.cA, p.cB, crt, C,
                          ldc, t0);
   }
   HIP_TRY(hipGetLastError());
@@ -539,32 +540,23 @@ void make_ozi_plan(int64_t m, int64_t n, int64_t k, int p, OziPlan* o) {
 // Stages, stopping after `last`: 0 scale, 1 encode A, 2 encode B, 3 limb
 // GEMM into the partial-sum planes, 4 reduction into C.
 int run_ozi(const OziPlan& p, DeviceState* d, const double* A, int64_t lda, const double* B,
-            int64_t ldb, double* C, int64_t ldc, int last, uint8_t* planes_a_out,
+            int64_t ldb, double* C, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
             uint8_t* planes_b_out) {
   uint8_t* ws = d->ws;
-  uint64_t* amax_a = reinterpret_cast<uint64_t*>(ws + p.off_amax_a);
-  uint64_t* amax_b = reinterpret_cast<uint64_t*>(ws + p.off_amax_b);
-  int* flag = reinterpret_cast<int*>(ws + p.off_flag);
   uint8_t* pa = planes_a_out ? planes_a_out : ws + p.off_pa;
   uint8_t* pb = planes_b_out ? planes_b_out : ws + p.off_pb;
   int64_t* H = reinterpret_cast<int64_t*>(ws + p.off_h);
+  ConvOperand a, b;
+  conv_operands(p, A, lda, B, ldb, p.cap, p.cap, ws, pa, pb, p.off_h, &a, &b);
 
   record(d, 0);
-  const int64_t nzero = (int64_t)((p.off_flag + 256 - p.off_amax_a) / sizeof(uint64_t));
-  hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(nzero, 256)), dim3(256), 0, g_stream,
-                     amax_a, nzero, (uint64_t)0);
-  launch_amax_f64(A, lda, B, ldb, p.m, p.n, p.k, amax_a, amax_b, flag);
-  HIP_TRY(hipGetLastError());
+  HIP_TRY(launch_line_max(g_stream, false, a, b, flag));
   record(d, 1);
   if (last < 1) return OZFP4_OK;
 
-  const int64_t nfa = (p.m_pad / kFragLines) * p.kblocks;
-  const int64_t nfb = (p.n_pad / kFragLines) * p.kblocks;
-  HIP_TRY(launch_encode_ozi((unsigned)encode_grid(nfa), g_stream, A, (int64_t)1, lda, p.m, p.k,
-                            amax_a, p.cap, pa, p.plane_a, nfa, p.kblocks, p.nplanes));
-  record(d, 2);
-  HIP_TRY(launch_encode_ozi((unsigned)encode_grid(nfb), g_stream, B, ldb, (int64_t)1, p.n, p.k,
-                            amax_b, p.cap, pb, p.plane_b, nfb, p.kblocks, p.nplanes));
+  HIP_TRY(encode_stages(d, a, b, [&](const ConvOperand& x, const ConvOperand& y) {
+    return launch_encode_ozi(g_stream, x, y, p.nplanes);
+  }));
   record(d, 3);
   if (last < 3) return OZFP4_OK;
 
@@ -573,8 +565,8 @@ int run_ozi(const OziPlan& p, DeviceState* d, const double* A, int64_t lda, cons
   record(d, 4);
   if (last < 4) return OZFP4_OK;
 
-  HIP_TRY(launch_ozi_reduce(g_stream, H, p.m_pad, p.m_pad * p.n_pad, p.nh, p.m, p.n, amax_a,
-                            amax_b, p.cap, C, ldc));
+  HIP_TRY(launch_ozi_reduce(g_stream, H, p.m_pad, p.m_pad * p.n_pad, p.nh, p.m, p.n, a.amax,
+                            b.amax, p.cap, C, ldc));
   record(d, 5);
   return OZFP4_OK;
 }
@@ -586,8 +578,9 @@ int prepare_ozi(int64_t m, int64_t n, int64_t k, int n_limbs, OziPlan* p, Device
   return ensure_workspace(*d, p->total);
 }
 
-int finish_with_flag(DeviceState* d, const int* dflag, int nstages) {
-  HIP_TRY(hipMemcpyAsync(d->h_flag, dflag, sizeof(int), hipMemcpyDeviceToHost, g_stream));
+// Waits for the call's kernels; the line maxima have set the flag word where
+// an input is not finite.
+int finish_with_flag(DeviceState* d, int nstages) {
   HIP_TRY(hipStreamSynchronize(g_stream));
   if (g_profile && nstages > 0) {
     g_pending_stages = 0;
@@ -598,7 +591,7 @@ int finish_with_flag(DeviceState* d, const int* dflag, int nstages) {
     }
     g_nstages = nstages;
   }
-  return *d->h_flag ? OZFP4_ENONFINITE : OZFP4_OK;
+  return *static_cast<volatile int*>(d->h_flag) ? OZFP4_ENONFINITE : OZFP4_OK;
 }
 
 // ------------------------------------------------------ two-term split
@@ -645,39 +638,25 @@ int make_split_plan(int64_t m, int64_t n, int64_t k, int L, SplitPlan* p) {
 // Stages: 0 scale, 1 encode A (both terms), 2 encode B (both terms), 3 the
 // four residue GEMMs, 4 the combined CRT.
 int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, const double* B,
-              int64_t ldb, double* C, int64_t ldc) {
+              int64_t ldb, double* C, int64_t ldc, int* flag) {
   const HostTables* T = tables();
   uint8_t* ws = d->ws;
-  uint64_t* amax_a = reinterpret_cast<uint64_t*>(ws + p.off_amax_a);
-  uint64_t* amax_b = reinterpret_cast<uint64_t*>(ws + p.off_amax_b);
-  int* flag = reinterpret_cast<int*>(ws + p.off_flag);
+  unsigned* arrive = reinterpret_cast<unsigned*>(ws + p.off_flag) + 32;
   const int L = p.L;
+  ConvOperand a, b;
+  conv_operands(p, A, lda, B, ldb, p.cA, p.cB, ws, ws + p.off_pa1, ws + p.off_pb1, p.off_r, &a, &b);
+  a.term_bytes = (int64_t)(p.off_pa2 - p.off_pa1);
+  b.term_bytes = (int64_t)(p.off_pb2 - p.off_pb1);
   record(d, 0);
-  const int64_t nzero = (int64_t)((p.off_flag + 256 - p.off_amax_a) / sizeof(uint64_t));
-  hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(nzero, 256)), dim3(256), 0, g_stream, amax_a,
-                     nzero, (uint64_t)0);
-  launch_amax_f64(A, lda, B, ldb, p.m, p.n, p.k, amax_a, amax_b, flag);
-  HIP_TRY(hipGetLastError());
+  HIP_TRY(launch_line_max(g_stream, false, a, b, flag));
   record(d, 1);
   // the moduli list: the greedy one, or one with one-limb heads
   const ModConst& mod = p.heads ? T->lists[p.heads].mod : T->mod;
   const ModConst* d_mod = p.heads ? d->lists[p.heads].mod : d->d_mod;
-  const uint16_t* d_lut = p.heads ? d->lists[p.heads].lut : d->d_lut;
-  const int lut_entries = mod.lut_off[L - 1] + 3 * mod.m[L - 1];
-  const size_t lut_bytes = sizeof(uint16_t) * (size_t)lut_entries;
-  const int64_t nfa = (p.m_pad / kFragLines) * p.kblocks;
-  const int64_t nfb = (p.n_pad / kFragLines) * p.kblocks;
-  for (int term = 0; term < 2; ++term)
-    HIP_TRY(launch_encode_split(term == 1, false, (unsigned)encode_grid(nfa), lut_bytes, g_stream, A,
-                                (int64_t)1, lda, p.m, p.k, amax_a, p.cA,
-                                ws + (term ? p.off_pa2 : p.off_pa1), p.plane_a, nfa, p.kblocks, L,
-                                d_mod, d_lut, lut_entries, p.d));
-  record(d, 2);
-  for (int term = 0; term < 2; ++term)
-    HIP_TRY(launch_encode_split(term == 1, false, (unsigned)encode_grid(nfb), lut_bytes, g_stream, B,
-                                ldb, (int64_t)1, p.n, p.k, amax_b, p.cB,
-                                ws + (term ? p.off_pb2 : p.off_pb1), p.plane_b, nfb, p.kblocks, L,
-                                d_mod, d_lut, lut_entries, p.d));
+  const uint16_t* lut = p.heads ? d->lists[p.heads].lut : d->d_lut;
+  HIP_TRY(encode_stages(d, a, b, [&](const ConvOperand& x, const ConvOperand& y) {
+    return launch_encode(g_stream, false, x, y, L, mod, d_mod, lut, 2, p.d);
+  }));
   record(d, 3);
   // residue sets: A1 B1, A1 B2, A2 B1, A2 B2; with heads, the heads by the
   // single-product GEMM, then the two-limb moduli from their planes on
@@ -695,7 +674,7 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
     if (Lg > 0)
       HIP_TRY(launch_gemm_res(ws + pa[q] + 2 * p.nh * p.plane_a, ws + pb[q] + 2 * p.nh * p.plane_b,
                               Rq + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
-                              p.n_pad, p.kblocks, Lg, d_tail, lockstep_counters(flag, q), d->cus_per_xcd));
+                              p.n_pad, p.kblocks, Lg, d_tail, arrive, d->cus_per_xcd));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
@@ -703,7 +682,7 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
   const int nc = (p.heads ? T->lists[p.heads].crt : T->crt)[L].nc;
   const CrtConst* crt = (p.heads ? d->lists[p.heads].crt : d->d_crt) + L;
   HIP_TRY(launch_crt_split(g_stream, nc, R, R + p.rset, R + 2 * p.rset, R + 3 * p.rset,
-                           p.m_pad, rplane, p.m, p.n, amax_a, amax_b, p.cA, p.cB, p.d,
+                           p.m_pad, rplane, p.m, p.n, a.amax, b.amax, p.cA, p.cB, p.d,
                            d_mod, crt, C, ldc));
   record(d, 5);
   return OZFP4_OK;
@@ -742,9 +721,9 @@ int ozfp4_dgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, c
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, nullptr, nullptr);
+  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 5);
+  return finish_with_flag(d, 5);
 }
 
 int ozfp4_init(void) {
@@ -783,10 +762,12 @@ int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_
   const bool captured = capture != hipStreamCaptureStatusNone;
   const bool profile = g_profile;
   if (captured) g_profile = false;
-  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, nullptr, nullptr, d->scratch);
+  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4,
+                 captured ? reinterpret_cast<int*>(d->scratch + p.off_flag) : start_flag(d), nullptr,
+                 nullptr, d->scratch);
   g_profile = profile;
   if (rc || captured) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->scratch + p.off_flag), 5);
+  return finish_with_flag(d, 5);
 }
 
 int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
@@ -812,9 +793,9 @@ int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t 
   if (rc) return rc;
   rc = ensure_workspace(d, p.total);
   if (rc) return rc;
-  rc = run_split(p, d, A, lda, B, ldb, C, ldc);
+  rc = run_split(p, d, A, lda, B, ldb, C, ldc, start_flag(d));
   if (rc) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 5);
+  return finish_with_flag(d, 5);
 }
 
 int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda, const int8_t* B,
@@ -886,9 +867,9 @@ int ozfp4_sgemm(int64_t m, int64_t n, int64_t k, const float* A, int64_t lda, co
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d, true);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, nullptr, nullptr);
+  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 5);
+  return finish_with_flag(d, 5);
 }
 
 int ozfp4_sgemm_capacity(int64_t k, int n_moduli, int32_t* c_a, int32_t* c_b) {
@@ -925,9 +906,9 @@ int ozfp4_dgemm_ozi(int64_t m, int64_t n, int64_t k, const double* A, int64_t ld
   DeviceState* d;
   rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
   if (rc) return rc;
-  rc = run_ozi(p, d, A, lda, B, ldb, C, ldc, 4, nullptr, nullptr);
+  rc = run_ozi(p, d, A, lda, B, ldb, C, ldc, 4, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 5);
+  return finish_with_flag(d, 5);
 }
 
 int ozfp4_ozi_config(int n_limbs, int32_t* capacity, int32_t* n_planes, int32_t* n_groups) {
@@ -950,9 +931,9 @@ int ozfp4_ozi_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int6
   DeviceState* d;
   rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
   if (rc) return rc;
-  rc = run_ozi(p, d, A, lda, B, ldb, nullptr, 0, 2, planes_a, planes_b);
+  rc = run_ozi(p, d, A, lda, B, ldb, nullptr, 0, 2, start_flag(d), planes_a, planes_b);
   if (rc) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 0);
+  return finish_with_flag(d, 0);
 }
 
 int ozfp4_ozi_partials(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
@@ -965,7 +946,7 @@ int ozfp4_ozi_partials(int64_t m, int64_t n, int64_t k, const double* A, int64_t
   DeviceState* d;
   rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
   if (rc) return rc;
-  rc = run_ozi(p, d, A, lda, B, ldb, nullptr, 0, 3, nullptr, nullptr);
+  rc = run_ozi(p, d, A, lda, B, ldb, nullptr, 0, 3, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
   for (int h = 0; h < p.nh; ++h) {
     HIP_TRY(hipMemcpy2DAsync(H + (size_t)h * ldh * n, (size_t)ldh * sizeof(int64_t),
@@ -973,7 +954,7 @@ int ozfp4_ozi_partials(int64_t m, int64_t n, int64_t k, const double* A, int64_t
                              (size_t)p.m_pad * sizeof(int64_t), (size_t)m * sizeof(int64_t),
                              (size_t)n, hipMemcpyDeviceToDevice, g_stream));
   }
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 0);
+  return finish_with_flag(d, 0);
 }
 
 int ozfp4_set_stream(void* stream) {
@@ -1115,14 +1096,13 @@ int ozfp4_scales(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, 
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 0, nullptr, nullptr);
+  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 0, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_shifts, dim3(blocks_for(m, 256)), dim3(256), 0, g_stream,
-                     reinterpret_cast<uint64_t*>(d->ws + p.off_amax_a), m, p.cA, s);
-  hipLaunchKernelGGL(k_shifts, dim3(blocks_for(n, 256)), dim3(256), 0, g_stream,
-                     reinterpret_cast<uint64_t*>(d->ws + p.off_amax_b), n, p.cB, t);
-  HIP_TRY(hipGetLastError());
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 0);
+  ConvOperand a, b;
+  conv_operands(p, A, lda, B, ldb, p.cA, p.cB, d->ws, nullptr, nullptr, p.off_r, &a, &b);
+  HIP_TRY(launch_shifts(g_stream, a, s));
+  HIP_TRY(launch_shifts(g_stream, b, t));
+  return finish_with_flag(d, 0);
 }
 
 int ozfp4_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
@@ -1136,9 +1116,9 @@ int ozfp4_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int64_t 
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 2, planes_a, planes_b);
+  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 2, start_flag(d), planes_a, planes_b);
   if (rc) return rc;
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 0);
+  return finish_with_flag(d, 0);
 }
 
 int ozfp4_residues(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
@@ -1151,14 +1131,14 @@ int ozfp4_residues(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 3, nullptr, nullptr);
+  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 3, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
   for (int l = 0; l < n_moduli; ++l) {
     HIP_TRY(hipMemcpy2DAsync(R + (size_t)l * ldr * n, (size_t)ldr,
                              d->ws + p.off_r + (size_t)l * p.m_pad * p.n_pad, (size_t)p.m_pad,
                              (size_t)m, (size_t)n, hipMemcpyDeviceToDevice, g_stream));
   }
-  return finish_with_flag(d, reinterpret_cast<int*>(d->ws + p.off_flag), 0);
+  return finish_with_flag(d, 0);
 }
 
 int ozfp4_calib_mfma(int64_t blocks, int64_t iterations, uint32_t seed, float* sink) {

@@ -1,8 +1,8 @@
 // Kernels of the two-term split route (ozfp4_dgemm_split), an extension of
 // Sec. IV-B for inputs whose rows or columns span wide exponent ranges: the
-// second-term encoder and the reconstruction that combines the three exact
-// products. A translation unit of its own, so nothing here can change how
-// the compiler schedules the default kernels.
+// reconstruction that combines the three exact products. A translation unit
+// of its own, so nothing here can change how the compiler schedules the
+// default kernels.
 #include "device_common.hpp"
 #include "crt_split.hpp"
 #include "split.hpp"
@@ -98,21 +98,6 @@ __global__ __launch_bounds__(256) void k_crt_split(
 }
 
 }  // namespace
-
-hipError_t launch_encode_split(bool second, bool wide, unsigned grid, size_t lds_bytes,
-                               hipStream_t stream, const double* X, int64_t rs, int64_t ks,
-                               int64_t lines, int64_t k, const uint64_t* amax, int cap,
-                               uint8_t* planes, int64_t plane_bytes, int64_t nfrag,
-                               int64_t kblocks, int L, const ModConst* mc, const void* lut,
-                               int lut_entries, int d2) {
-  auto kern = second ? (wide ? k_encode_dgemm<false, true, double, true>
-                             : k_encode_dgemm<false, false, double, true>)
-                     : (wide ? k_encode_dgemm<false, true, double, false>
-                             : k_encode_dgemm<false, false, double, false>);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds_bytes, stream, X, rs, ks, lines, k, amax,
-                     cap, planes, plane_bytes, nfrag, kblocks, L, mc, lut, lut_entries, d2);
-  return hipGetLastError();
-}
 
 hipError_t launch_crt_split(hipStream_t stream, int nc, const uint8_t* R11, const uint8_t* R12a,
                             const uint8_t* R12b, const uint8_t* R22, int64_t ldr, int64_t rplane,
