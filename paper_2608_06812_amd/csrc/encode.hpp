@@ -171,6 +171,18 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
   }
 }
 
+// Moduli that one wave encodes its fragment for. A wave takes about 0.5 us a
+// modulus, so small operands give each fragment to several waves (which
+// convert its values again, from L2) as long as that makes no more than 4096
+// waves, four a SIMD: both operands 41 -> 9 us at 64^3, 53 -> 36 us at
+// 1024^3 (18 moduli); with 8192 waves 42 us at 1024^3, with 2048 as with 4096.
+constexpr int64_t kEncodeWaves = 4096;
+inline int moduli_per_group(const ConvOperand& a, const ConvOperand& b, int L, int terms) {
+  const int64_t frags = ((int64_t)a.blocks * a.kfrags + (int64_t)b.blocks * b.kfrags) * terms;
+  const int64_t groups = std::min<int64_t>(L, std::max<int64_t>(1, kEncodeWaves / std::max<int64_t>(1, frags)));
+  return (int)((L + groups - 1) / groups);
+}
+
 // Launches the encoder over both operands. `mod` is the host copy of mc;
 // terms: 2 for the two-term split.
 template <bool kKar, bool kWide, typename TIn>
@@ -178,7 +190,7 @@ hipError_t launch_encode_kernel(hipStream_t stream, const ConvOperand& a, const 
                                 int L, const ModConst& mod, const ModConst* mc, const void* lut,
                                 int terms, int d2) {
   const uint32_t ba = encode_blocks(a), bb = encode_blocks(b);
-  const int per_group = L;
+  const int per_group = moduli_per_group(a, b, L, terms);
   const int groups = (L + per_group - 1) / per_group;
   const size_t entry = kKar ? sizeof(uint32_t) : sizeof(uint16_t);
   size_t lds = 0;

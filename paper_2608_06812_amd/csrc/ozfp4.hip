@@ -335,12 +335,23 @@ static_assert(2 * 8 * kMaxChunks <= kTile * OZFP4_MIN_MODULI, "partial maxima ex
 template <class Plan>
 void conv_operands(const Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb, int cA,
                    int cB, uint8_t* ws, uint8_t* pa, uint8_t* pb, size_t off_part, ConvOperand* a,
-                   ConvOperand* b) {
+                   ConvOperand* b, int64_t kfrags = 0) {
   uint64_t* part = reinterpret_cast<uint64_t*>(ws + off_part);
   *a = conv_operand(A, 1, lda, p.m, p.k, cA, p.m_pad, p.kblocks, p.plane_a, pa,
                     reinterpret_cast<uint64_t*>(ws + p.off_amax_a), part);
   *b = conv_operand(B, ldb, 1, p.n, p.k, cB, p.n_pad, p.kblocks, p.plane_b, pb,
                     reinterpret_cast<uint64_t*>(ws + p.off_amax_b), part + a->nchunk * p.m_pad);
+  if (kfrags > 0)
+    for (ConvOperand* op : {a, b}) {
+      op->blocks = (uint32_t)((op->lines + kFragLines - 1) / kFragLines);
+      op->kfrags = (uint32_t)kfrags;
+    }
+}
+
+// Fragments of a line block that the residue GEMMs of a call read: those
+// that k touches for the short one, the layout's for every other kernel.
+int64_t frags_read(bool short_only, int64_t k, int64_t kblocks) {
+  return short_only ? (k + kFragK - 1) / kFragK : kblocks;
 }
 
 // A conversion stage's encoder: `launch` takes both operands in one launch;
@@ -407,7 +418,13 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
   uint8_t* R = ws + p.off_r;
   const int L = p.L;
   ConvOperand a, b;
-  conv_operands(p, Av, lda, Bv, ldb, p.cA, p.cB, ws, pa, pb, p.off_r, &a, &b);
+  // planes that only this call's GEMMs read go without the padding lines (a
+  // line's codes reach no other line's outputs, and a code has no NaN), the
+  // hook's get every byte of the layout
+  const bool short_only =
+      !p.kar && p.nh == 0 && use_short_gemm(p.m, p.n, p.k, p.L);
+  conv_operands(p, Av, lda, Bv, ldb, p.cA, p.cB, ws, pa, pb, p.off_r, &a, &b,
+                planes_a_out ? 0 : frags_read(short_only, p.k, p.kblocks));
 
   record(d, 0);
   // stage 0: line maxima
@@ -547,7 +564,8 @@ int run_ozi(const OziPlan& p, DeviceState* d, const double* A, int64_t lda, cons
   uint8_t* pb = planes_b_out ? planes_b_out : ws + p.off_pb;
   int64_t* H = reinterpret_cast<int64_t*>(ws + p.off_h);
   ConvOperand a, b;
-  conv_operands(p, A, lda, B, ldb, p.cap, p.cap, ws, pa, pb, p.off_h, &a, &b);
+  conv_operands(p, A, lda, B, ldb, p.cap, p.cap, ws, pa, pb, p.off_h, &a, &b,
+                planes_a_out ? 0 : p.kblocks);
 
   record(d, 0);
   HIP_TRY(launch_line_max(g_stream, false, a, b, flag));
@@ -644,7 +662,9 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
   unsigned* arrive = reinterpret_cast<unsigned*>(ws + p.off_flag) + 32;
   const int L = p.L;
   ConvOperand a, b;
-  conv_operands(p, A, lda, B, ldb, p.cA, p.cB, ws, ws + p.off_pa1, ws + p.off_pb1, p.off_r, &a, &b);
+  const bool short_only = p.nh == 0 && use_short_gemm(p.m, p.n, p.k, L);
+  conv_operands(p, A, lda, B, ldb, p.cA, p.cB, ws, ws + p.off_pa1, ws + p.off_pb1, p.off_r, &a, &b,
+                frags_read(short_only, p.k, p.kblocks));
   a.term_bytes = (int64_t)(p.off_pa2 - p.off_pa1);
   b.term_bytes = (int64_t)(p.off_pb2 - p.off_pb1);
   record(d, 0);
