@@ -89,8 +89,10 @@ constexpr int kEncWaves = 4;   // waves of an encoder block, one fragment each
 // turn: every XCD then carries the same mix of moduli, the blocks an XCD
 // runs together share the A and B panels of one modulus in its L2, and all
 // XCDs stream the same B panels at about the same time. Otherwise each XCD
-// takes a contiguous range of the flattened (modulus, tile) order. Tiles
-// are ordered in groups of kGroupM tile rows.
+// takes a contiguous range of the flattened (modulus, tile) order, and so it
+// does below min_share tiles, where an eighth of the grid is too few tiles to
+// share panels in an XCD's L2. Tiles are ordered in groups of kGroupM tile
+// rows.
 #ifndef OZFP4_GROUP_M
 #define OZFP4_GROUP_M 4
 #endif
@@ -98,11 +100,12 @@ constexpr int kGroupM = OZFP4_GROUP_M;
 // A grid holds fewer than 2^32 work-items, so every count here is below 2^24
 // and the divisions are 32-bit ones.
 __device__ __forceinline__ void tile_coords(unsigned bid, int64_t nblocks, int64_t tiles_m,
-                                            int64_t tiles_n, int* l, int64_t* tm, int64_t* tn) {
+                                            int64_t tiles_n, int* l, int64_t* tm, int64_t* tn,
+                                            unsigned min_share = 8) {
   const unsigned xcd = bid & 7, local = bid >> 3;
   const unsigned T = (unsigned)(tiles_m * tiles_n);
   unsigned t;
-  if ((T & 7) == 0) {
+  if ((T & 7) == 0 && T >= min_share) {
     const unsigned per = T >> 3;
     const unsigned li = local / per;
     *l = (int)li;

@@ -1,6 +1,8 @@
 // The residue GEMM for short products: few stages or few tiles. A
 // translation unit of its own, so nothing here can change how the compiler
 // schedules the default kernels.
+#include <algorithm>
+
 #include "device_common.hpp"
 #include "gemm_short.hpp"
 
@@ -23,6 +25,12 @@ constexpr int kShortFrags = 16;
 constexpr int kShortStage = kShortFrags * kFragBytes;
 constexpr int kShortDma = kShortFrags / kShortWaves;   // 4
 
+// Up to 64 tiles an XCD takes whole moduli: eight XCDs with eight tiles or
+// fewer of each modulus fetch every panel into most L2s (512 x 512 x 4096:
+// 58 us at 5.1 TB/s from beyond L2, 46 us with whole moduli; 1024^3 41.9 and
+// 39.5); at 256 tiles the shared order is ahead again (2048^3 228 and 231).
+constexpr unsigned kShortMinShare = 72;
+
 // LDS offset of fragment (plane p, line block rb / cb)
 __device__ __forceinline__ constexpr int fragAs(int p, int rb) { return (p * 4 + rb) * kFragBytes; }
 __device__ __forceinline__ constexpr int fragBs(int p, int cb) { return (8 + p * 4 + cb) * kFragBytes; }
@@ -30,15 +38,15 @@ __device__ __forceinline__ constexpr int fragBs(int p, int cb) { return (8 + p *
 template <bool kSkipA1B1>
 __device__ __forceinline__ void gemm_short_tile(
     uint8_t* lds, int l, int64_t tm, int64_t tn, const uint8_t* __restrict__ PA,
-    const uint8_t* __restrict__ PB, uint8_t* __restrict__ R, int64_t plane_a, int64_t plane_b,
-    int64_t kblocks, int nst, int64_t ldr, int64_t rplane, const ModConst* __restrict__ mc) {
+    const uint8_t* __restrict__ PB, uint8_t* __restrict__ Rl, int64_t plane_a, int64_t plane_b,
+    int64_t kblocks, int st0, int nst, int64_t ldr, int m) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int rbw = 2 * wm, cbw = 2 * wn;   // this wave's first A / B line block
 
   // Wave w copies operand w / 2, plane w % 2: its four line blocks j. The
-  // line blocks are kblocks KiB apart; stage s is at s KiB in each. One
+  // line blocks are kblocks KiB apart; stage s is st0 + s KiB into each. One
   // descriptor covers all (4 kblocks KiB, below 2^31 for k <= 2^24).
   const uint8_t* base = wave < 2 ? PA + (int64_t)(2 * l + wave) * plane_a + tm * 4 * kblocks * kFragBytes
                                  : PB + (int64_t)(2 * l + wave - 2) * plane_b + tn * 4 * kblocks * kFragBytes;
@@ -47,7 +55,7 @@ __device__ __forceinline__ void gemm_short_tile(
       __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)(4 * row), kBufferWord3);
   const int lane16 = lane * 16;
   auto dma = [&](int st, int j) {
-    dma16_buf(src, (uint32_t)lane16, (uint32_t)j * row + (uint32_t)st * kFragBytes,
+    dma16_buf(src, (uint32_t)lane16, (uint32_t)j * row + (uint32_t)(st0 + st) * kFragBytes,
               lds + (st % kShortRing) * kShortStage + (wave * kShortDma + j) * kFragBytes);
   };
 
@@ -175,36 +183,105 @@ __device__ __forceinline__ void gemm_short_tile(
     if (s + 1 < nst) stage(Odd{}, s + 1, nst - 2 - s);
   }
 
-  store_residues_by_k<kSkipA1B1, 1>(acc, (int64_t)nst * kFragK, mc->m[l], R + (int64_t)l * rplane,
-                                    ldr, tm * kShortTile + wm * 64, tn * kShortTile + wn * 64, lane);
+  store_residues_by_k<kSkipA1B1, 1>(acc, (int64_t)nst * kFragK, m, Rl, ldr,
+                                    tm * kShortTile + wm * 64, tn * kShortTile + wn * 64, lane);
 }
 
-__global__ __launch_bounds__(kShortWaves * 64, 2) void k_gemm_short(
-    const uint8_t* __restrict__ PA, const uint8_t* __restrict__ PB, uint8_t* __restrict__ R,
-    int64_t plane_a, int64_t plane_b, int64_t kblocks, int nst, int64_t tiles_m, int64_t tiles_n,
-    int64_t nblocks, int64_t ldr, int64_t rplane, const ModConst* __restrict__ mc) {
+// Block order: sets (product, k range) take the place of moduli in the tile
+// mapping, each with its nmod moduli.
+__global__ __launch_bounds__(kShortWaves * 64, 2) void k_gemm_short(ShortGemm g, int nst,
+                                                                    int64_t tiles_m,
+                                                                    int64_t tiles_n,
+                                                                    int64_t nblocks) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kShortRing * kShortStage];
-  int l;
+  int u;
   int64_t tm, tn;
-  tile_coords(blockIdx.x, nblocks, tiles_m, tiles_n, &l, &tm, &tn);
-  if (mc->m[l] == 169)
-    gemm_short_tile<true>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, nst, ldr, rplane, mc);
+  tile_coords(blockIdx.x, nblocks, tiles_m, tiles_n, &u, &tm, &tn, kShortMinShare);
+  const int set = u / g.nmod, l = u - set * g.nmod;
+  const int q = set / g.nsplit, part = set - q * g.nsplit;
+  const int st0 = nst * part / g.nsplit, st1 = nst * (part + 1) / g.nsplit;
+  const uint8_t* pa = g.pa + (q >> 1) * g.term_a;
+  const uint8_t* pb = g.pb + (q & 1) * g.term_b;
+  uint8_t* Rl = (part == 0 ? g.R + q * g.rset
+                           : g.partial + (int64_t)(q * (g.nsplit - 1) + part - 1) * g.nmod * g.rplane) +
+                l * g.rplane;
+  const int m = g.mc->m[l];
+  if (m == 169)
+    gemm_short_tile<true>(lds, l, tm, tn, pa, pb, Rl, g.plane_a, g.plane_b, g.kblocks, st0,
+                          st1 - st0, g.ldr, m);
   else
-    gemm_short_tile<false>(lds, l, tm, tn, PA, PB, R, plane_a, plane_b, kblocks, nst, ldr, rplane, mc);
+    gemm_short_tile<false>(lds, l, tm, tn, pa, pb, Rl, g.plane_a, g.plane_b, g.kblocks, st0,
+                           st1 - st0, g.ldr, m);
 }
+
+// R += the partial residues, modulo m: one thread per four rows of a column
+// of one residue plane (blockIdx.y = product and modulus).
+__global__ __launch_bounds__(256) void k_add_partials(ShortGemm g, uint32_t rows4,
+                                                      uint32_t threads) {
+  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= threads) return;
+  const int q = (int)blockIdx.y / g.nmod, l = (int)blockIdx.y - q * g.nmod;
+  const uint32_t col = t / rows4;
+  const int64_t off = l * g.rplane + (int64_t)col * g.ldr + (int64_t)(t - col * rows4) * 4;
+  uint32_t* r = reinterpret_cast<uint32_t*>(g.R + q * g.rset + off);
+  const uint8_t* x = g.partial + (int64_t)q * (g.nsplit - 1) * g.nmod * g.rplane + off;
+  uint32_t lo = *r & 0x00ff00ffu, hi = (*r >> 8) & 0x00ff00ffu;   // sums <= 16 * 168
+  for (int part = 1; part < g.nsplit; ++part) {
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(x);
+    lo += w & 0x00ff00ffu;
+    hi += (w >> 8) & 0x00ff00ffu;
+    x += g.nmod * g.rplane;
+  }
+  const uint32_t m = (uint32_t)g.mc->m[l];
+  *r = ((lo & 0xffffu) % m) | (((hi & 0xffffu) % m) << 8) | (((lo >> 16) % m) << 16) |
+       (((hi >> 16) % m) << 24);
+}
+
+int stages_of(int64_t k) { return (int)((k + kFragK - 1) / kFragK); }
 
 }  // namespace
 
-hipError_t launch_gemm_short(hipStream_t stream, const uint8_t* pa, const uint8_t* pb, uint8_t* R,
-                             int64_t ldr, int64_t rplane, int64_t plane_a, int64_t plane_b,
-                             int64_t m, int64_t n, int64_t k, int64_t kblocks, int nmod,
-                             const ModConst* mc) {
-  const int64_t tiles_m = (m + kShortTile - 1) / kShortTile, tiles_n = (n + kShortTile - 1) / kShortTile;
-  const int64_t nblocks = tiles_m * tiles_n * nmod;
-  const int nst = (int)((k + kFragK - 1) / kFragK);
-  hipLaunchKernelGGL(k_gemm_short, dim3((unsigned)nblocks), dim3(kShortWaves * 64), 0, stream, pa,
-                     pb, R, plane_a, plane_b, kblocks, nst, tiles_m, tiles_n, nblocks, ldr, rplane,
-                     mc);
+// Estimated time in us of the blocks cut into ns ranges each. 512 blocks run
+// at a time, two a CU; a stage takes 0.47 us there, 0.27 us where the last
+// round leaves every block its own CU; 2.5 us around a block's stages; the
+// second launch 4.5 us and the partial residues' traffic. Measured (GEMM
+// stage, one range / the ranges this chooses): 128 x 128 x 8192, 19 moduli,
+// 38.5 / 18.2 us; 128 x 128 x 2048 15.4 / 13.3; 300 x 300 x 20000 112 / 87;
+// 7 x 5 x 50000 202 / 55; 500 x 400 x 60000 615 / 311 (513 with 256 x 128
+// tiles); no case of 64 .. 1024 a side slower.
+static double short_gemm_us(int64_t blocks, int nst, int ns, double residues) {
+  const int64_t total = blocks * ns, rounds = total / 512, rest = total % 512;
+  const double stages = (double)((nst + ns - 1) / ns);
+  double t = (double)rounds * (stages * 0.47 + 2.5);
+  if (rest > 0) t += stages * (rest <= 256 ? 0.27 : 0.47) + 2.5;
+  if (ns > 1) t += 4.5 + 0.3 * ns + (double)(ns - 1) * residues * 2.0 / 4e6;
+  return t;
+}
+
+int short_gemm_split(int64_t m, int64_t n, int64_t k, int nmod, int nprod) {
+  const int64_t blocks = ((m + kShortTile - 1) / kShortTile) * ((n + kShortTile - 1) / kShortTile) *
+                         nmod * nprod;
+  const int nst = stages_of(k);
+  if (blocks == 0 || blocks > 1024) return 1;   // two rounds and more: nothing to gain
+  const double residues = (double)(m * n) * nmod * nprod;
+  int best = 1;
+  for (int ns = 2; ns <= 16 && nst / ns >= 8; ++ns)
+    if (short_gemm_us(blocks, nst, ns, residues) < short_gemm_us(blocks, nst, best, residues))
+      best = ns;
+  return best;
+}
+
+hipError_t launch_gemm_short(hipStream_t stream, const ShortGemm& g) {
+  const int64_t tiles_m = (g.m + kShortTile - 1) / kShortTile;
+  const int64_t tiles_n = (g.n + kShortTile - 1) / kShortTile;
+  const int64_t nblocks = tiles_m * tiles_n * g.nmod * g.nprod * g.nsplit;
+  hipLaunchKernelGGL(k_gemm_short, dim3((unsigned)nblocks), dim3(kShortWaves * 64), 0, stream, g,
+                     stages_of(g.k), tiles_m, tiles_n, nblocks);
+  if (g.nsplit > 1) {
+    const uint32_t rows4 = (uint32_t)((g.m + 3) / 4), threads = rows4 * (uint32_t)g.n;
+    hipLaunchKernelGGL(k_add_partials, dim3((threads + 255) / 256, g.nmod * g.nprod), dim3(256), 0,
+                       stream, g, rows4, threads);
+  }
   return hipGetLastError();
 }
 

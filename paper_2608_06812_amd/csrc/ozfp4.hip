@@ -203,8 +203,9 @@ struct DgemmPlan {
   int heads;                 // one-limb heads of the list (0: the greedy list)
   int nh;                    // of them among the call's L moduli: min(heads, L)
   int nplanes;               // planes per operand: 2L, plus the sum planes in the Karatsuba mode
-  // workspace offsets
-  size_t off_amax_a, off_amax_b, off_flag, off_pa, off_pb, off_r, total;
+  int nsplit;                // k ranges of the short residue GEMM
+  // workspace offsets; total_x: with the k ranges' partial residues at off_x
+  size_t off_amax_a, off_amax_b, off_flag, off_pa, off_pb, off_r, total, off_x, total_x;
 };
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -227,6 +228,32 @@ int check_dgemm_args(int64_t m, int64_t n, int64_t k, const void* A, int64_t lda
     if (k > OZFP4_MAX_K) return OZFP4_EKBOUND;
   }
   return OZFP4_OK;
+}
+
+// Which residue GEMM: the 256 x 128 tile's block has a CU to itself and pays
+// about 7 us around its stages, the 128 x 128 tile (gemm_short.hip) overlaps
+// them with a second block but moves a third more operand bytes. GEMM stage,
+// us, 256 x 128 against 128 x 128, 18 moduli: 63 / 42 at 1024^3, 916 / 571 at
+// 6000 x 6000 x 384, 2328 / 1966 at 6000 x 6000 x 2048, 1885 / 1759 at 4096^3,
+// 29833 / 27431 at 16384 x 16384 x 4096, 13839 / 13820 and 13792 / 13427 at
+// 8192^3, 6690 / 6699 at 4096 x 4096 x 16384, 107793 / 113244 at 16384^3: the
+// line lies at k = 6144. Under four blocks per CU the smaller tile also
+// leaves fewer CUs idle (69 / 39 at 128 x 128 x 8192).
+bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
+  const int64_t blocks = ((m + kTileM - 1) / kTileM) * ((n + kTileN - 1) / kTileN) * nmod;
+  return k <= 6144 || blocks < 1024;
+}
+
+// Sets nsplit and off_x of a plan whose other fields are set; total_x is
+// total plus the partial residues of the k ranges.
+template <class Plan>
+void plan_split(Plan* p, int nprod, bool kar) {
+  const int nmod = p->L - p->nh;
+  p->nsplit = !kar && nmod > 0 && use_short_gemm(p->m, p->n, p->k, nmod)
+                  ? short_gemm_split(p->m, p->n, p->k, nmod, nprod)
+                  : 1;
+  p->off_x = p->total;
+  p->total_x = align256(p->total + (size_t)(p->nsplit - 1) * nprod * nmod * p->m_pad * p->n_pad);
 }
 
 // FP32 emulation: an FP32 significand's 24 bits in place of FP64's 53
@@ -259,6 +286,7 @@ int make_dgemm_plan(int64_t m, int64_t n, int64_t k, int L, DgemmPlan* p, bool f
   p->off_pb = off;     off = align256(off + (size_t)p->plane_b * p->nplanes);
   p->off_r = off;      off = align256(off + (size_t)p->m_pad * p->n_pad * L);
   p->total = off;
+  plan_split(p, 1, p->kar);
   return OZFP4_OK;
 }
 
@@ -370,38 +398,59 @@ hipError_t encode_stages(DeviceState* d, const ConvOperand& a, const ConvOperand
   return rc;
 }
 
-// Which residue GEMM: the 256 x 128 tile's block has a CU to itself and pays
-// about 7 us around its stages, the 128 x 128 tile (gemm_short.hip) overlaps
-// them with a second block but moves a third more operand bytes. GEMM stage,
-// us, 256 x 128 against 128 x 128, 18 moduli: 63 / 42 at 1024^3, 916 / 571 at
-// 6000 x 6000 x 384, 2328 / 1966 at 6000 x 6000 x 2048, 1885 / 1759 at 4096^3,
-// 29833 / 27431 at 16384 x 16384 x 4096, 13839 / 13820 and 13792 / 13427 at
-// 8192^3, 6690 / 6699 at 4096 x 4096 x 16384, 107793 / 113244 at 16384^3: the
-// line lies at k = 6144. Under four blocks per CU the smaller tile also
-// leaves fewer CUs idle (69 / 39 at 128 x 128 x 8192).
-bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
-  const int64_t blocks = ((m + kTileM - 1) / kTileM) * ((n + kTileN - 1) / kTileN) * nmod;
-  return k <= 6144 || blocks < 1024;
+// The residue GEMMs of nmod two-limb moduli (of one product, or the four of
+// the two-term split), with the arguments of the short one. arrive: eight
+// lockstep counters.
+hipError_t launch_gemm_res(const ShortGemm& g, unsigned* arrive, int cus_per_xcd) {
+  if (use_short_gemm(g.m, g.n, g.k, g.nmod)) return launch_gemm_short(g_stream, g);
+  const int64_t tiles_m = (g.m + kTileM - 1) / kTileM, tiles_n = (g.n + kTileN - 1) / kTileN;
+  const int64_t nblocks = tiles_m * tiles_n * g.nmod;
+  for (int q = 0; q < g.nprod; ++q) {
+    hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, g_stream,
+                       reinterpret_cast<uint64_t*>(arrive), (int64_t)4, (uint64_t)0);
+    hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream,
+                       g.pa + (q >> 1) * g.term_a, g.pb + (q & 1) * g.term_b, g.R + q * g.rset,
+                       g.plane_a, g.plane_b, g.kblocks, tiles_m, tiles_n, nblocks, g.ldr, g.rplane,
+                       g.mc, arrive, (unsigned)cus_per_xcd);
+  }
+  return hipGetLastError();
 }
 
-// The residue GEMM of the nmod two-limb moduli of mc, from their planes pa,
-// pb into their residue planes R (leading dimension m_pad). arrive: eight
-// lockstep counters.
-hipError_t launch_gemm_res(const uint8_t* pa, const uint8_t* pb, uint8_t* R, int64_t plane_a,
-                           int64_t plane_b, int64_t m, int64_t n, int64_t k, int64_t m_pad,
-                           int64_t n_pad, int64_t kblocks, int nmod, const ModConst* mc,
-                           unsigned* arrive, int cus_per_xcd) {
-  if (use_short_gemm(m, n, k, nmod))
-    return launch_gemm_short(g_stream, pa, pb, R, m_pad, m_pad * n_pad, plane_a, plane_b, m, n, k,
-                             kblocks, nmod, mc);
-  const int64_t tiles_m = m_pad / kTileM, tiles_n = (n + kTileN - 1) / kTileN;
-  const int64_t nblocks = tiles_m * tiles_n * nmod;
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, g_stream, reinterpret_cast<uint64_t*>(arrive),
-                     (int64_t)4, (uint64_t)0);
-  hipLaunchKernelGGL(k_gemm_res, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa, pb,
-                     R, plane_a, plane_b, kblocks, tiles_m, tiles_n, nblocks, m_pad, m_pad * n_pad,
-                     mc, arrive, (unsigned)cus_per_xcd);
-  return hipGetLastError();
+// The two-limb moduli of a call: after the heads of its list.
+template <class Plan>
+ShortGemm gemm_of(const Plan& p, DeviceState* d, uint8_t* ws, const uint8_t* pa, const uint8_t* pb,
+                  uint8_t* R) {
+  const int64_t rplane = p.m_pad * p.n_pad;
+  ShortGemm g = {};
+  g.pa = pa + 2 * p.nh * p.plane_a;
+  g.pb = pb + 2 * p.nh * p.plane_b;
+  g.R = R + p.nh * rplane;
+  g.partial = ws + p.off_x;
+  g.plane_a = p.plane_a;
+  g.plane_b = p.plane_b;
+  g.ldr = p.m_pad;
+  g.rplane = rplane;
+  g.m = p.m;
+  g.n = p.n;
+  g.k = p.k;
+  g.kblocks = p.kblocks;
+  g.nmod = p.L - p.nh;
+  g.nprod = 1;
+  g.nsplit = p.nsplit;
+  g.mc = p.heads ? d->lists[p.heads].tail : d->d_mod;
+  return g;
+}
+
+// The workspace of a plan: without the ranges' residues, and so without the
+// ranges, where it cannot be had with them.
+template <class Plan>
+int ensure_plan(DeviceState* d, Plan* p) {
+  int rc = ensure_workspace(d, p->total_x);
+  if (rc == OZFP4_ENOMEM && p->nsplit > 1) {
+    p->nsplit = 1;
+    rc = ensure_workspace(d, p->total);
+  }
+  return rc;
 }
 
 // Stages of the dgemm pipeline, stopping after `last`:
@@ -455,11 +504,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
     // before the CRT reads
     HIP_TRY(launch_gemm_one_limb(g_stream, pa, pb, R, p.m_pad, rplane, p.plane_a, p.plane_b,
                                  p.m_pad, p.n_pad, p.kblocks, p.nh, d->lists[p.heads].head));
-    if (Lg > 0)
-      HIP_TRY(launch_gemm_res(pa + 2 * p.nh * p.plane_a, pb + 2 * p.nh * p.plane_b,
-                              R + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
-                              p.n_pad, p.kblocks, Lg, d->lists[p.heads].tail, arrive,
-                              d->cus_per_xcd));
+    if (Lg > 0) HIP_TRY(launch_gemm_res(gemm_of(p, d, ws, pa, pb, R), arrive, d->cus_per_xcd));
   } else if (p.kar) {
     const int64_t tiles_m = p.m_pad / kTileM, tiles_n = (p.n + kTileN - 1) / kTileN;
     const int64_t nblocks = tiles_m * tiles_n * L;
@@ -467,8 +512,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
                                 p.kblocks, tiles_m, tiles_n, nblocks, p.m_pad, p.m_pad * p.n_pad,
                                 d->d_mod, L));
   } else {
-    HIP_TRY(launch_gemm_res(pa, pb, R, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad, p.n_pad,
-                            p.kblocks, L, d->d_mod, arrive, d->cus_per_xcd));
+    HIP_TRY(launch_gemm_res(gemm_of(p, d, ws, pa, pb, R), arrive, d->cus_per_xcd));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
@@ -621,7 +665,9 @@ struct SplitPlan {
   int L, cA, cB, d;
   int heads, nh;             // one-limb heads of the list, and of them among the L moduli
   int64_t m_pad, n_pad, k_pad, kblocks, plane_a, plane_b, rset;
-  size_t off_amax_a, off_amax_b, off_flag, off_pa1, off_pa2, off_pb1, off_pb2, off_r, total;
+  int nsplit;                // as in DgemmPlan
+  size_t off_amax_a, off_amax_b, off_flag, off_pa1, off_pa2, off_pb1, off_pb2, off_r, total, off_x,
+      total_x;
 };
 
 int make_split_plan(int64_t m, int64_t n, int64_t k, int L, SplitPlan* p) {
@@ -650,6 +696,7 @@ int make_split_plan(int64_t m, int64_t n, int64_t k, int L, SplitPlan* p) {
   p->off_pb2 = off;    off = align256(off + (size_t)p->plane_b * 2 * L);
   p->off_r = off;      off = align256(off + (size_t)p->rset * 4);
   p->total = off;
+  plan_split(p, 4, false);
   return OZFP4_OK;
 }
 
@@ -684,17 +731,19 @@ int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, 
   const int64_t rplane = p.m_pad * p.n_pad;
   const size_t pa[4] = {p.off_pa1, p.off_pa1, p.off_pa2, p.off_pa2};
   const size_t pb[4] = {p.off_pb1, p.off_pb2, p.off_pb1, p.off_pb2};
-  const ModConst* d_tail = p.heads ? d->lists[p.heads].tail : d->d_mod;
-  for (int q = 0; q < 4; ++q) {
-    uint8_t* Rq = ws + p.off_r + (size_t)q * p.rset;
-    if (p.heads)
-      HIP_TRY(launch_gemm_one_limb(g_stream, ws + pa[q], ws + pb[q], Rq, p.m_pad, rplane,
-                                   p.plane_a, p.plane_b, p.m_pad, p.n_pad, p.kblocks, p.nh,
+  if (p.heads)
+    for (int q = 0; q < 4; ++q)
+      HIP_TRY(launch_gemm_one_limb(g_stream, ws + pa[q], ws + pb[q],
+                                   ws + p.off_r + (size_t)q * p.rset, p.m_pad, rplane, p.plane_a,
+                                   p.plane_b, p.m_pad, p.n_pad, p.kblocks, p.nh,
                                    d->lists[p.heads].head));
-    if (Lg > 0)
-      HIP_TRY(launch_gemm_res(ws + pa[q] + 2 * p.nh * p.plane_a, ws + pb[q] + 2 * p.nh * p.plane_b,
-                              Rq + p.nh * rplane, p.plane_a, p.plane_b, p.m, p.n, p.k, p.m_pad,
-                              p.n_pad, p.kblocks, Lg, d_tail, arrive, d->cus_per_xcd));
+  if (Lg > 0) {
+    ShortGemm g = gemm_of(p, d, ws, ws + p.off_pa1, ws + p.off_pb1, ws + p.off_r);
+    g.nprod = 4;
+    g.term_a = a.term_bytes;
+    g.term_b = b.term_bytes;
+    g.rset = p.rset;
+    HIP_TRY(launch_gemm_res(g, arrive, d->cus_per_xcd));
   }
   HIP_TRY(hipGetLastError());
   record(d, 4);
@@ -714,7 +763,7 @@ int prepare(int64_t m, int64_t n, int64_t k, int L, DgemmPlan* p, DeviceState** 
   if (rc) return rc;
   rc = device_state(d);
   if (rc) return rc;
-  return ensure_workspace(*d, p->total);
+  return ensure_plan(*d, p);
 }
 
 }  // namespace
@@ -774,6 +823,7 @@ int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_
   rc = make_dgemm_plan(m, n, k, n_moduli, &p);
   if (rc) return rc;
   if (p.total > (size_t)OZFP4_SCRATCH_BYTES) return OZFP4_ESCRATCH;
+  if (p.total_x > (size_t)OZFP4_SCRATCH_BYTES) p.nsplit = 1;
   // under stream capture the kernels are recorded into the caller's graph:
   // no stage events, and no read-back of the non-finite flag (that would
   // synchronize the capturing stream)
@@ -811,7 +861,7 @@ int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t 
   if (rc) return rc;
   rc = device_state(&d);
   if (rc) return rc;
-  rc = ensure_workspace(d, p.total);
+  rc = ensure_plan(d, &p);
   if (rc) return rc;
   rc = run_split(p, d, A, lda, B, ldb, C, ldc, start_flag(d));
   if (rc) return rc;

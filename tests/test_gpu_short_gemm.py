@@ -5,7 +5,8 @@ the ring's fill (1 to 6 stages), of the tile (127 to 129 lines) and of the
 residue composition's ranges of k (1280 / 1281 and 17472 / 17473, where the
 sums of 4 (acc0 + 13 acc1 + 169 acc2) and of 4 (acc1 + 13 acc2) reach 2^24
 at most). Constant operands drive the sums towards those bounds: every
-product of a modulus then has the same sign and limbs."""
+product of a modulus then has the same sign and limbs. Long inner dimensions
+over few tiles run in several k ranges."""
 
 import numpy as np
 import pytest
@@ -34,6 +35,11 @@ CASES = [
     (64, 64, 17472, 18, "constant"),
     (64, 64, 17473, 18, "constant"),
     (40, 150, 70000, 19, "constant"),
+    # k cut into ranges whose residues are added modulo m
+    (129, 257, 2049, 27, "random"),
+    (300, 290, 3000, 18, "constant"),
+    (500, 400, 9000, 16, "random"),
+    (1030, 900, 700, 18, "random"),
 ]
 
 
@@ -62,3 +68,43 @@ def test_residues_of_short_products(gpu_lib, m, n, k, L, kind):
         rb = o.residues(Bi, q).astype(np.float64)
         want = np.mod(np.rint(ra @ rb).astype(np.int64), q)
         assert np.array_equal(R[l].T.astype(np.int64), want), f"modulus {q}"
+
+
+def test_split_route_in_k_ranges(gpu_lib):
+    """The four products of the two-term split in one launch, k in ranges,
+    with and without one-limb heads: entries of few bits, whose product FP64
+    holds exactly."""
+    rng = np.random.default_rng(SEED)
+    m, n, k = 130, 100, 5000
+    A = rng.integers(-1000, 1001, size=(m, k)).astype(np.float64)
+    B = rng.integers(-1000, 1001, size=(k, n)).astype(np.float64)
+    want = A @ B
+    announce("split in k ranges")
+    try:
+        for heads, L in ((0, 19), (4, 21)):
+            gpu_lib.ozfp4_set_one_limb_moduli(heads)
+            C = to_np(gpu_lib.dgemm_split(dev_cm(A), dev_cm(B), L))
+            assert np.array_equal(C, want)
+            assert np.array_equal(to_np(gpu_lib.dgemm(dev_cm(A), dev_cm(B), L)), want)
+    finally:
+        gpu_lib.ozfp4_set_one_limb_moduli(0)
+
+
+def test_noalloc_without_room_for_the_ranges(gpu_lib):
+    """A call whose planes and residues just fit the scratch array runs with
+    one k range (its other ranges' residues would not fit), with the
+    workspace call's bits."""
+    import torch
+    m, n, k, L = 200, 180, 28928, 18
+    assert gpu_lib.ozfp4_init() == gpu_lib.OZFP4_OK
+    A, B = dgemm_inputs(m, n, k, 0.5, SEED)
+    Ad, Bd = dev_cm(A), dev_cm(B)
+    out = torch.zeros((n, m), dtype=torch.float64, device="cuda").t()
+    announce("noalloc at the scratch limit")
+    gpu_lib.dgemm_noalloc(Ad, Bd, out, L)
+    assert torch.equal(out, gpu_lib.dgemm(Ad, Bd, L))
+    Ad = dev_cm(np.ones((m, k + 256)))
+    Bd = dev_cm(np.ones((k + 256, n)))
+    with pytest.raises(gpu_lib.OzFP4Error) as e:
+        gpu_lib.dgemm_noalloc(Ad, Bd, out, L)
+    assert e.value.code == gpu_lib.OZFP4_ESCRATCH
