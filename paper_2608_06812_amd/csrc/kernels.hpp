@@ -1,5 +1,5 @@
-// gfx950 kernels of the default path: the INT8 encoder, the residue GEMM,
-// the INT8 GEMM and the CRT. Included by
+// gfx950 kernels of the default path: the residue GEMM, the INT8 GEMM and the
+// CRT. Included by
 // ozfp4.hip only (the Karatsuba kernels live in karatsuba.hip, a separate
 // translation unit, so that their code cannot change how the compiler
 // schedules these).
@@ -27,50 +27,6 @@ __global__ void k_fill_i32_matrix(int32_t* __restrict__ C, int64_t m, int64_t n,
   const int64_t total = m * n, stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride)
     C[(t % m) + (t / m) * ldc] = 0;
-}
-
-// INT8 encoder (Sec. III): three greedy limbs per value from a 256-entry
-// table (codes of c0, c1, c2 in bits 0-3, 4-7, 8-11), three planes.
-__global__ __launch_bounds__(256) void k_encode_s8(
-    const int8_t* __restrict__ X, int64_t rs, int64_t ks, int64_t lines, int64_t k,
-    uint8_t* __restrict__ planes, int64_t plane_bytes, int64_t nfrag, int64_t kblocks,
-    const uint16_t* __restrict__ lut8) {
-  __shared__ uint16_t s_lut[256];
-  s_lut[threadIdx.x] = lut8[threadIdx.x];
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  for (int64_t f = (int64_t)blockIdx.x * kEncWaves + wave; f < nfrag;
-       f += (int64_t)gridDim.x * kEncWaves) {
-    const int64_t rb = f / kblocks, kb = f - rb * kblocks;
-    const int64_t line = rb * kFragLines + (lane & 31);
-    const int64_t kbase = kb * kFragK + (lane >> 5) * 32;
-    const bool live = line < lines;
-    const int8_t* src = X + line * rs;
-    uint32_t w[3][4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint32_t a0 = 0, a1 = 0, a2 = 0;
-#pragma unroll
-      for (int e8 = 0; e8 < 8; ++e8) {
-        const int64_t kk = kbase + g * 8 + e8;
-        int v = (live && kk < k) ? (int)src[kk * ks] : 0;
-        uint32_t E = s_lut[v + 128];
-        a0 |= (E & 0xfu) << (4 * e8);
-        a1 |= ((E >> 4) & 0xfu) << (4 * e8);
-        a2 |= ((E >> 8) & 0xfu) << (4 * e8);
-      }
-      w[0][g] = a0;
-      w[1][g] = a1;
-      w[2][g] = a2;
-    }
-    uint8_t* out = planes + f * kFragBytes + lane * 16;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      v4i v = {(int)w[p][0], (int)w[p][1], (int)w[p][2], (int)w[p][3]};
-      *reinterpret_cast<v4i*>(out + (int64_t)p * plane_bytes) = v;
-    }
-  }
 }
 
 // The residue GEMM over all moduli (Sec. VI-D): one block tile of one

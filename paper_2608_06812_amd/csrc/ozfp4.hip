@@ -11,6 +11,7 @@
 #include "calibrate.hpp"
 #include "convert.hpp"
 #include "gemm_short.hpp"
+#include "igemm.hpp"
 #include "karatsuba.hpp"
 #include "kernels.hpp"
 #include "onelimb.hpp"
@@ -244,6 +245,22 @@ bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
   return k <= 6144 || blocks < 1024;
 }
 
+// Which INT8 GEMM: 128 x 128 tiles, one block a CU (k_gemm_s8), or 128 x 64
+// tiles, two blocks a CU and half again as many operand bytes per MFMA
+// (igemm.hip). GEMM, us, in that order: 17.5 / 14.2 at 1000^3, 79 / 73 at
+// 6000 x 6000 x 384, 70 / 68 at 4096 x 4096 x 1024, 461 / 462 at 8192 x 8192
+// x 2048, 220 / 227 at 4096^3, 1661 / 1721 at 8192^3: the line lies at k =
+// 1024. Beyond it the smaller tile, with k ranges, wins where the larger
+// leaves more than 15 % of its rounds' CUs idle (72 / 15 at 164 x 152 x 7877,
+// 816 / 99 at 500 x 500 x 100000; 2048^3, one full round, 35.1 / 35.5).
+bool use_short_s8(int64_t m, int64_t n, int64_t k) {
+  if (k <= 1024) return true;
+  if ((k + kS8ShortRange - 1) / kS8ShortRange > 16) return false;
+  const int64_t blocks = ((m + kTileS8M - 1) / kTileS8M) * ((n + kTileS8N - 1) / kTileS8N);
+  const int64_t slots = (blocks + 255) / 256 * 256;
+  return blocks * 100 < slots * 85;
+}
+
 // Sets nsplit and off_x of a plan whose other fields are set; total_x is
 // total plus the partial residues of the k ranges.
 template <class Plan>
@@ -314,12 +331,6 @@ void record(DeviceState* d, int i) {
   if (!g_profile) return;
   if (i == 0) (void)resolve_pending();   // before its events are recorded over
   (void)hipEventRecord(d->ev[i], g_stream);
-}
-
-int encode_grid(int64_t nfrag) {
-  // enough blocks to fill the chip several times, each wave loops
-  int64_t want = (nfrag + kEncWaves - 1) / kEncWaves;
-  return (int)std::min<int64_t>(want, 256 * 16);
 }
 
 // The flag word of a call about to start, zero: the line-maximum kernel
@@ -890,23 +901,53 @@ int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda
   const int64_t m_pad = round_up(m, kTile), n_pad = round_up(n, kTile);
   const int64_t k_pad = plane_k_pad(k), kblocks = k_pad / kFragK;
   const int64_t plane_a = m_pad * k_pad / 2, plane_b = n_pad * k_pad / 2;
+  const bool use_short = use_short_s8(m, n, k);
+  int nsplit = use_short ? short_s8_split(m, n, k) : 1;
   const size_t off_pb = align256((size_t)plane_a * 3);
-  rc = ensure_workspace(d, off_pb + align256((size_t)plane_b * 3));
+  const size_t off_x = off_pb + align256((size_t)plane_b * 3);
+  auto partials = [&](int ranges) {
+    return ranges > 1 ? sizeof(int32_t) * (size_t)ranges * m_pad * n_pad : 0;
+  };
+  rc = ensure_workspace(d, off_x + partials(nsplit));
+  if (rc == OZFP4_ENOMEM && nsplit > 1 && k <= kS8ShortRange) {
+    nsplit = 1;
+    rc = ensure_workspace(d, off_x);
+  }
   if (rc) return rc;
   uint8_t* pa = d->ws;
   uint8_t* pb = d->ws + off_pb;
   record(d, 0);
-  const int64_t nfa = (m_pad / kFragLines) * kblocks, nfb = (n_pad / kFragLines) * kblocks;
-  hipLaunchKernelGGL(k_encode_s8, dim3(encode_grid(nfa)), dim3(256), 0, g_stream, A, (int64_t)1,
-                     lda, m, k, pa, plane_a, nfa, kblocks, d->d_lut8);
-  record(d, 1);
-  hipLaunchKernelGGL(k_encode_s8, dim3(encode_grid(nfb)), dim3(256), 0, g_stream, B, ldb,
-                     (int64_t)1, n, k, pb, plane_b, nfb, kblocks, d->d_lut8);
+  // the padding lines stay as they are (a line's codes reach no other line's
+  // outputs); k is padded as far as the GEMM reads
+  auto operand = [&](const int8_t* X, int64_t rs, int64_t ks, int64_t lines, uint8_t* planes,
+                     int64_t plane_bytes) {
+    const int64_t blocks = (lines + kFragLines - 1) / kFragLines;
+    return S8Operand{X, rs, ks, lines, k, planes, plane_bytes, kblocks, (uint32_t)blocks,
+                     (uint32_t)frags_read(use_short, k, kblocks)};
+  };
+  S8Operand a = operand(A, 1, lda, m, pa, plane_a), b = operand(B, ldb, 1, n, pb, plane_b);
+  if (g_profile) {   // each operand its own launch, and so its own stage time
+    S8Operand none = a;
+    none.blocks = 0;
+    HIP_TRY(launch_encode_s8(g_stream, a, none, d->d_lut8));
+    record(d, 1);
+    none = b;
+    none.blocks = 0;
+    HIP_TRY(launch_encode_s8(g_stream, none, b, d->d_lut8));
+  } else {
+    HIP_TRY(launch_encode_s8(g_stream, a, b, d->d_lut8));
+  }
   record(d, 2);
-  const int64_t tiles_m = m_pad / kTileS8M, tiles_n = n_pad / kTileS8N;
-  const int64_t nblocks = tiles_m * tiles_n;
-  hipLaunchKernelGGL(k_gemm_s8, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa, pb, C,
-                     plane_a, plane_b, kblocks, tiles_m, tiles_n, nblocks, m, n, ldc);
+  if (use_short) {
+    HIP_TRY(launch_gemm_s8_short(g_stream, ShortS8{pa, pb, C, reinterpret_cast<int32_t*>(d->ws + off_x),
+                                                   plane_a, plane_b, kblocks, m, n, k, ldc, m_pad,
+                                                   n_pad, nsplit}));
+  } else {
+    const int64_t tiles_m = (m + kTileS8M - 1) / kTileS8M, tiles_n = (n + kTileS8N - 1) / kTileS8N;
+    const int64_t nblocks = tiles_m * tiles_n;
+    hipLaunchKernelGGL(k_gemm_s8, dim3((unsigned)nblocks), dim3(kWaves * 64), 0, g_stream, pa, pb, C,
+                       plane_a, plane_b, kblocks, tiles_m, tiles_n, nblocks, m, n, ldc);
+  }
   record(d, 3);
   HIP_TRY(hipGetLastError());
   if (g_profile) {
