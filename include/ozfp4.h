@@ -174,6 +174,32 @@ int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k,
                    const int8_t* B, int64_t ldb,
                    int32_t* C, int64_t ldc);
 
+/* Entry points that ozfp4_product can run. */
+#define OZFP4_OP_DGEMM 0
+#define OZFP4_OP_DGEMM_NOALLOC 1
+#define OZFP4_OP_DGEMM_SPLIT 2
+#define OZFP4_OP_DGEMM_OZI 3
+#define OZFP4_OP_SGEMM 4
+#define OZFP4_OP_IGEMM_S8 5
+
+/*
+ * ozfp4_product -- one of the products above for operands in either storage
+ * order: element (i, j) of A (m x k) at A[i * a_rs + j * a_cs], of B (k x n)
+ * at B[i * b_rs + j * b_cs], in elements of the entry point's input type.
+ * One stride of each operand is 1 and the other at least the extent that
+ * runs along it (column-major: rs = 1, cs >= rows; row-major: cs = 1, rs >=
+ * columns), else OZFP4_EINVAL. C is column-major with leading dimension ldc.
+ * The conversion reads either order directly, so a row-major caller needs no
+ * transposed copy. count: n_moduli, or n_limbs for OZFP4_OP_DGEMM_OZI;
+ * ignored by OZFP4_OP_IGEMM_S8; 0 with OZFP4_OP_SGEMM takes the fewest
+ * moduli with 24-bit capacities. Result, errors and synchronization are the
+ * entry point's; OZFP4_EINVAL for an unknown op.
+ */
+int ozfp4_product(int op, int64_t m, int64_t n, int64_t k,
+                  const void* A, int64_t a_rs, int64_t a_cs,
+                  const void* B, int64_t b_rs, int64_t b_cs,
+                  void* C, int64_t ldc, int count);
+
 /* Stream for subsequent calls (a hipStream_t; NULL = the null stream). */
 int ozfp4_set_stream(void* stream);
 

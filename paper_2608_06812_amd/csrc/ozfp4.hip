@@ -219,10 +219,15 @@ bool dims_ok(int64_t m, int64_t n, int64_t k) {
   return ok(m, n) && ok(m, k) && ok(n, k);
 }
 
-int check_dgemm_args(int64_t m, int64_t n, int64_t k, const void* A, int64_t lda, const void* B,
-                     int64_t ldb, int n_moduli) {
+// Column-major operands (BLAS): leading dimensions in range.
+bool leading_ok(int64_t m, int64_t k, int64_t lda, int64_t ldb) {
+  return lda >= std::max<int64_t>(1, m) && ldb >= std::max<int64_t>(1, k);
+}
+
+int check_dgemm_args(int64_t m, int64_t n, int64_t k, const void* A, const void* B, bool layouts_ok,
+                     int n_moduli) {
   if (!dims_ok(m, n, k)) return OZFP4_EINVAL;
-  if (lda < std::max<int64_t>(1, m) || ldb < std::max<int64_t>(1, k)) return OZFP4_EINVAL;
+  if (!layouts_ok) return OZFP4_EINVAL;
   if (n_moduli < OZFP4_MIN_MODULI || n_moduli > OZFP4_MAX_MODULI) return OZFP4_EMODULI;
   if (m > 0 && n > 0 && k > 0) {
     if (!A || !B) return OZFP4_EINVAL;
@@ -342,6 +347,17 @@ int* start_flag(DeviceState* d) {
   return d->h_flag_dev;
 }
 
+// A caller's matrix: element (i, j) at X[i * rs + j * cs], one of the strides
+// 1.
+struct Mat {
+  const void* X;
+  int64_t rs, cs;
+};
+
+bool layout_ok(int64_t rows, int64_t cols, int64_t rs, int64_t cs) {
+  return (rs == 1 && cs >= std::max<int64_t>(1, rows)) || (cs == 1 && rs >= std::max<int64_t>(1, cols));
+}
+
 // One operand of a conversion stage over the padded layout; its partial
 // line maxima go to part.
 ConvOperand conv_operand(const void* X, int64_t rs, int64_t ks, int64_t lines, int64_t k, int cap,
@@ -366,19 +382,19 @@ ConvOperand conv_operand(const void* X, int64_t rs, int64_t ks, int64_t lines, i
   return op;
 }
 
-// The operands A (m x k) and B (k x n) of a plan, column-major. Their partial
+// The operands A (m x k) and B (k x n) of a plan. Their partial
 // maxima lie where the residues (scheme I: the partial sums) will be written
 // after the encoder has read them: (m_pad + n_pad) 8 kMaxChunks bytes at
 // most, and those take at least 512 max(m_pad, n_pad).
 static_assert(2 * 8 * kMaxChunks <= kTile * OZFP4_MIN_MODULI, "partial maxima exceed the residues");
 template <class Plan>
-void conv_operands(const Plan& p, const void* A, int64_t lda, const void* B, int64_t ldb, int cA,
-                   int cB, uint8_t* ws, uint8_t* pa, uint8_t* pb, size_t off_part, ConvOperand* a,
-                   ConvOperand* b, int64_t kfrags = 0) {
+void conv_operands(const Plan& p, const Mat& A, const Mat& B, int cA, int cB, uint8_t* ws,
+                   uint8_t* pa, uint8_t* pb, size_t off_part, ConvOperand* a, ConvOperand* b,
+                   int64_t kfrags = 0) {
   uint64_t* part = reinterpret_cast<uint64_t*>(ws + off_part);
-  *a = conv_operand(A, 1, lda, p.m, p.k, cA, p.m_pad, p.kblocks, p.plane_a, pa,
+  *a = conv_operand(A.X, A.rs, A.cs, p.m, p.k, cA, p.m_pad, p.kblocks, p.plane_a, pa,
                     reinterpret_cast<uint64_t*>(ws + p.off_amax_a), part);
-  *b = conv_operand(B, ldb, 1, p.n, p.k, cB, p.n_pad, p.kblocks, p.plane_b, pb,
+  *b = conv_operand(B.X, B.cs, B.rs, p.n, p.k, cB, p.n_pad, p.kblocks, p.plane_b, pb,
                     reinterpret_cast<uint64_t*>(ws + p.off_amax_b), part + a->nchunk * p.m_pad);
   if (kfrags > 0)
     for (ConvOperand* op : {a, b}) {
@@ -467,8 +483,7 @@ int ensure_plan(DeviceState* d, Plan* p) {
 // Stages of the dgemm pipeline, stopping after `last`:
 // 0 scale, 1 encode A, 2 encode B, 3 residue GEMM, 4 CRT.
 // A, B and C are double, or float when p.f32.
-int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, const void* Bv,
-              int64_t ldb, void* Cv, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
+int run_dgemm(const DgemmPlan& p, DeviceState* d, const Mat& A, const Mat& B, void* Cv, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
               uint8_t* planes_b_out, uint8_t* ws_base = nullptr) {
   const HostTables* T = tables();
   uint8_t* ws = ws_base ? ws_base : d->ws;
@@ -483,7 +498,7 @@ int run_dgemm(const DgemmPlan& p, DeviceState* d, const void* Av, int64_t lda, c
   // hook's get every byte of the layout
   const bool short_only =
       !p.kar && p.nh == 0 && use_short_gemm(p.m, p.n, p.k, p.L);
-  conv_operands(p, Av, lda, Bv, ldb, p.cA, p.cB, ws, pa, pb, p.off_r, &a, &b,
+  conv_operands(p, A, B, p.cA, p.cB, ws, pa, pb, p.off_r, &a, &b,
                 planes_a_out ? 0 : frags_read(short_only, p.k, p.kblocks));
 
   record(d, 0);
@@ -575,10 +590,10 @@ struct OziPlan {
   size_t off_amax_a, off_amax_b, off_flag, off_pa, off_pb, off_h, total;
 };
 
-int check_ozi_args(int64_t m, int64_t n, int64_t k, const void* A, int64_t lda, const void* B,
-                   int64_t ldb, int n_limbs) {
+int check_ozi_args(int64_t m, int64_t n, int64_t k, const void* A, const void* B, bool layouts_ok,
+                   int n_limbs) {
   if (!dims_ok(m, n, k)) return OZFP4_EINVAL;
-  if (lda < std::max<int64_t>(1, m) || ldb < std::max<int64_t>(1, k)) return OZFP4_EINVAL;
+  if (!layouts_ok) return OZFP4_EINVAL;
   if (n_limbs < 1 || n_limbs > OZFP4_OZI_MAX_LIMBS) return OZFP4_EINVAL;
   if (m > 0 && n > 0 && k > 0) {
     if (!A || !B) return OZFP4_EINVAL;
@@ -611,15 +626,14 @@ void make_ozi_plan(int64_t m, int64_t n, int64_t k, int p, OziPlan* o) {
 
 // Stages, stopping after `last`: 0 scale, 1 encode A, 2 encode B, 3 limb
 // GEMM into the partial-sum planes, 4 reduction into C.
-int run_ozi(const OziPlan& p, DeviceState* d, const double* A, int64_t lda, const double* B,
-            int64_t ldb, double* C, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
+int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
             uint8_t* planes_b_out) {
   uint8_t* ws = d->ws;
   uint8_t* pa = planes_a_out ? planes_a_out : ws + p.off_pa;
   uint8_t* pb = planes_b_out ? planes_b_out : ws + p.off_pb;
   int64_t* H = reinterpret_cast<int64_t*>(ws + p.off_h);
   ConvOperand a, b;
-  conv_operands(p, A, lda, B, ldb, p.cap, p.cap, ws, pa, pb, p.off_h, &a, &b,
+  conv_operands(p, A, B, p.cap, p.cap, ws, pa, pb, p.off_h, &a, &b,
                 planes_a_out ? 0 : p.kblocks);
 
   record(d, 0);
@@ -713,15 +727,14 @@ int make_split_plan(int64_t m, int64_t n, int64_t k, int L, SplitPlan* p) {
 
 // Stages: 0 scale, 1 encode A (both terms), 2 encode B (both terms), 3 the
 // four residue GEMMs, 4 the combined CRT.
-int run_split(const SplitPlan& p, DeviceState* d, const double* A, int64_t lda, const double* B,
-              int64_t ldb, double* C, int64_t ldc, int* flag) {
+int run_split(const SplitPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C, int64_t ldc, int* flag) {
   const HostTables* T = tables();
   uint8_t* ws = d->ws;
   unsigned* arrive = reinterpret_cast<unsigned*>(ws + p.off_flag) + 32;
   const int L = p.L;
   ConvOperand a, b;
   const bool short_only = p.nh == 0 && use_short_gemm(p.m, p.n, p.k, L);
-  conv_operands(p, A, lda, B, ldb, p.cA, p.cB, ws, ws + p.off_pa1, ws + p.off_pb1, p.off_r, &a, &b,
+  conv_operands(p, A, B, p.cA, p.cB, ws, ws + p.off_pa1, ws + p.off_pb1, p.off_r, &a, &b,
                 frags_read(short_only, p.k, p.kblocks));
   a.term_bytes = (int64_t)(p.off_pa2 - p.off_pa1);
   b.term_bytes = (int64_t)(p.off_pb2 - p.off_pb1);
@@ -777,13 +790,11 @@ int prepare(int64_t m, int64_t n, int64_t k, int L, DgemmPlan* p, DeviceState** 
   return ensure_plan(*d, p);
 }
 
-}  // namespace
+// ------------------------------------------------------------ entry points
 
-extern "C" {
-
-int ozfp4_dgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
-                int64_t ldb, double* C, int64_t ldc, int n_moduli) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
+int dgemm_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
+               bool layouts_ok, double* C, int64_t ldc, int n_moduli){
+  int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
   if (m == 0 || n == 0) return OZFP4_OK;
@@ -801,19 +812,15 @@ int ozfp4_dgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, c
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, start_flag(d), nullptr, nullptr);
+  rc = run_dgemm(p, d, A, B, C, ldc, 4, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
   return finish_with_flag(d, 5);
 }
 
-int ozfp4_init(void) {
-  DeviceState* d;
-  return device_state(&d);
-}
 
-int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
-                        const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
+int dgemm_noalloc_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
+                       bool layouts_ok, double* C, int64_t ldc, int n_moduli){
+  int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
   if (m == 0 || n == 0) return OZFP4_OK;
@@ -843,7 +850,7 @@ int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_
   const bool captured = capture != hipStreamCaptureStatusNone;
   const bool profile = g_profile;
   if (captured) g_profile = false;
-  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4,
+  rc = run_dgemm(p, d, A, B, C, ldc, 4,
                  captured ? reinterpret_cast<int*>(d->scratch + p.off_flag) : start_flag(d), nullptr,
                  nullptr, d->scratch);
   g_profile = profile;
@@ -851,9 +858,10 @@ int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_
   return finish_with_flag(d, 5);
 }
 
-int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
-                      const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
+
+int dgemm_split_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
+                     bool layouts_ok, double* C, int64_t ldc, int n_moduli){
+  int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
   if (m == 0 || n == 0) return OZFP4_OK;
@@ -874,17 +882,69 @@ int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t 
   if (rc) return rc;
   rc = ensure_plan(d, &p);
   if (rc) return rc;
-  rc = run_split(p, d, A, lda, B, ldb, C, ldc, start_flag(d));
+  rc = run_split(p, d, A, B, C, ldc, start_flag(d));
   if (rc) return rc;
   return finish_with_flag(d, 5);
 }
 
-int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda, const int8_t* B,
-                   int64_t ldb, int32_t* C, int64_t ldc) {
+
+int sgemm_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
+               bool layouts_ok, float* C, int64_t ldc, int n_moduli){
+  int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
+  if (rc) return rc;
+  if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
+  if (m == 0 || n == 0) return OZFP4_OK;
+  if (!C) return OZFP4_EINVAL;
+  if (k == 0) {
+    DeviceState* d;
+    rc = device_state(&d);
+    if (rc) return rc;
+    // +0.0f has the bit pattern of the int32 zero
+    hipLaunchKernelGGL(k_fill_i32_matrix, dim3(stride_blocks(m * n, 256)), dim3(256), 0, g_stream,
+                       reinterpret_cast<int32_t*>(C), m, n, ldc);
+    HIP_TRY(hipGetLastError());
+    return OZFP4_OK;
+  }
+  DgemmPlan p;
+  DeviceState* d;
+  rc = prepare(m, n, k, n_moduli, &p, &d, true);
+  if (rc) return rc;
+  rc = run_dgemm(p, d, A, B, C, ldc, 4, start_flag(d), nullptr, nullptr);
+  if (rc) return rc;
+  return finish_with_flag(d, 5);
+}
+
+
+int dgemm_ozi_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
+                   bool layouts_ok, double* C, int64_t ldc, int n_limbs){
+  int rc = check_ozi_args(m, n, k, A.X, B.X, layouts_ok, n_limbs);
+  if (rc) return rc;
+  if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
+  if (m == 0 || n == 0) return OZFP4_OK;
+  if (!C) return OZFP4_EINVAL;
+  if (k == 0) {
+    DeviceState* d;
+    rc = device_state(&d);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_fill_f64_matrix, dim3(stride_blocks(m * n, 256)), dim3(256), 0, g_stream, C,
+                       m, n, ldc);
+    HIP_TRY(hipGetLastError());
+    return OZFP4_OK;
+  }
+  OziPlan p;
+  DeviceState* d;
+  rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
+  if (rc) return rc;
+  rc = run_ozi(p, d, A, B, C, ldc, 4, start_flag(d), nullptr, nullptr);
+  if (rc) return rc;
+  return finish_with_flag(d, 5);
+}
+
+
+int igemm_s8_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
+                  bool layouts_ok, int32_t* C, int64_t ldc){
   if (!dims_ok(m, n, k)) return OZFP4_EINVAL;
-  if (lda < std::max<int64_t>(1, m) || ldb < std::max<int64_t>(1, k) ||
-      ldc < std::max<int64_t>(1, m))
-    return OZFP4_EINVAL;
+  if (!layouts_ok || ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
   if (m == 0 || n == 0) return OZFP4_OK;
   if (!C) return OZFP4_EINVAL;
   if (k > OZFP4_MAX_K_S8) return OZFP4_EKBOUND;
@@ -897,11 +957,11 @@ int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda
     HIP_TRY(hipGetLastError());
     return OZFP4_OK;
   }
-  if (!A || !B) return OZFP4_EINVAL;
+  if (!A.X || !B.X) return OZFP4_EINVAL;
   const int64_t m_pad = round_up(m, kTile), n_pad = round_up(n, kTile);
   const int64_t k_pad = plane_k_pad(k), kblocks = k_pad / kFragK;
   const int64_t plane_a = m_pad * k_pad / 2, plane_b = n_pad * k_pad / 2;
-  const bool use_short = use_short_s8(m, n, k);
+  bool use_short = use_short_s8(m, n, k);
   int nsplit = use_short ? short_s8_split(m, n, k) : 1;
   const size_t off_pb = align256((size_t)plane_a * 3);
   const size_t off_x = off_pb + align256((size_t)plane_b * 3);
@@ -909,8 +969,8 @@ int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda
     return ranges > 1 ? sizeof(int32_t) * (size_t)ranges * m_pad * n_pad : 0;
   };
   rc = ensure_workspace(d, off_x + partials(nsplit));
-  if (rc == OZFP4_ENOMEM && nsplit > 1 && k <= kS8ShortRange) {
-    nsplit = 1;
+  if (rc == OZFP4_ENOMEM && nsplit > 1) {   // no room for the ranges' sums
+    use_short = false;
     rc = ensure_workspace(d, off_x);
   }
   if (rc) return rc;
@@ -919,13 +979,13 @@ int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda
   record(d, 0);
   // the padding lines stay as they are (a line's codes reach no other line's
   // outputs); k is padded as far as the GEMM reads
-  auto operand = [&](const int8_t* X, int64_t rs, int64_t ks, int64_t lines, uint8_t* planes,
+  auto operand = [&](const void* X, int64_t rs, int64_t ks, int64_t lines, uint8_t* planes,
                      int64_t plane_bytes) {
     const int64_t blocks = (lines + kFragLines - 1) / kFragLines;
-    return S8Operand{X, rs, ks, lines, k, planes, plane_bytes, kblocks, (uint32_t)blocks,
+    return S8Operand{static_cast<const int8_t*>(X), rs, ks, lines, k, planes, plane_bytes, kblocks, (uint32_t)blocks,
                      (uint32_t)frags_read(use_short, k, kblocks)};
   };
-  S8Operand a = operand(A, 1, lda, m, pa, plane_a), b = operand(B, ldb, 1, n, pb, plane_b);
+  S8Operand a = operand(A.X, A.rs, A.cs, m, pa, plane_a), b = operand(B.X, B.cs, B.rs, n, pb, plane_b);
   if (g_profile) {   // each operand its own launch, and so its own stage time
     S8Operand none = a;
     none.blocks = 0;
@@ -957,30 +1017,74 @@ int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda
   return OZFP4_OK;
 }
 
-int ozfp4_sgemm(int64_t m, int64_t n, int64_t k, const float* A, int64_t lda, const float* B,
-                int64_t ldb, float* C, int64_t ldc, int n_moduli) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
-  if (rc) return rc;
-  if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
-  if (m == 0 || n == 0) return OZFP4_OK;
-  if (!C) return OZFP4_EINVAL;
-  if (k == 0) {
-    DeviceState* d;
-    rc = device_state(&d);
-    if (rc) return rc;
-    // +0.0f has the bit pattern of the int32 zero
-    hipLaunchKernelGGL(k_fill_i32_matrix, dim3(stride_blocks(m * n, 256)), dim3(256), 0, g_stream,
-                       reinterpret_cast<int32_t*>(C), m, n, ldc);
-    HIP_TRY(hipGetLastError());
-    return OZFP4_OK;
+
+// The fewest moduli that give ozfp4_sgemm 24-bit capacities for this k
+// (OZFP4_MAX_MODULI if none does).
+int sgemm_moduli(int64_t k) {
+  const HostTables* T = tables();
+  if (T)
+    for (int L = OZFP4_MIN_MODULI; L <= OZFP4_MAX_MODULI; ++L) {
+      int a, b;
+      if (capacity_split(g_heads ? T->lists[g_heads].P[L] : T->P[L], std::max<int64_t>(1, k),
+                         kFp32Capacity, &a, &b) &&
+          a == kFp32Capacity && b == kFp32Capacity)
+        return L;
+    }
+  return OZFP4_MAX_MODULI;
+}
+
+}  // namespace
+
+extern "C" {
+
+int ozfp4_dgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
+                const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
+  return dgemm_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+}
+
+int ozfp4_product(int op, int64_t m, int64_t n, int64_t k, const void* A, int64_t a_rs,
+                  int64_t a_cs, const void* B, int64_t b_rs, int64_t b_cs, void* C, int64_t ldc,
+                  int count) {
+  const Mat a{A, a_rs, a_cs}, b{B, b_rs, b_cs};
+  const bool ok = layout_ok(m, k, a_rs, a_cs) && layout_ok(k, n, b_rs, b_cs);
+  double* c64 = static_cast<double*>(C);
+  switch (op) {
+    case OZFP4_OP_DGEMM: return dgemm_call(m, n, k, a, b, ok, c64, ldc, count);
+    case OZFP4_OP_DGEMM_NOALLOC: return dgemm_noalloc_call(m, n, k, a, b, ok, c64, ldc, count);
+    case OZFP4_OP_DGEMM_SPLIT: return dgemm_split_call(m, n, k, a, b, ok, c64, ldc, count);
+    case OZFP4_OP_DGEMM_OZI: return dgemm_ozi_call(m, n, k, a, b, ok, c64, ldc, count);
+    case OZFP4_OP_SGEMM:
+      return sgemm_call(m, n, k, a, b, ok, static_cast<float*>(C), ldc,
+                        count == 0 ? sgemm_moduli(k) : count);
+    case OZFP4_OP_IGEMM_S8:
+      return igemm_s8_call(m, n, k, a, b, ok, static_cast<int32_t*>(C), ldc);
+    default: return OZFP4_EINVAL;
   }
-  DgemmPlan p;
+}
+
+int ozfp4_init(void) {
   DeviceState* d;
-  rc = prepare(m, n, k, n_moduli, &p, &d, true);
-  if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, C, ldc, 4, start_flag(d), nullptr, nullptr);
-  if (rc) return rc;
-  return finish_with_flag(d, 5);
+  return device_state(&d);
+}
+
+int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
+                        const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
+  return dgemm_noalloc_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+}
+
+int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
+                      const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
+  return dgemm_split_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+}
+
+int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda,
+                   const int8_t* B, int64_t ldb, int32_t* C, int64_t ldc) {
+  return igemm_s8_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc);
+}
+
+int ozfp4_sgemm(int64_t m, int64_t n, int64_t k, const float* A, int64_t lda,
+                const float* B, int64_t ldb, float* C, int64_t ldc, int n_moduli) {
+  return sgemm_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
 }
 
 int ozfp4_sgemm_capacity(int64_t k, int n_moduli, int32_t* c_a, int32_t* c_b) {
@@ -999,27 +1103,7 @@ int ozfp4_sgemm_capacity(int64_t k, int n_moduli, int32_t* c_a, int32_t* c_b) {
 
 int ozfp4_dgemm_ozi(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                     const double* B, int64_t ldb, double* C, int64_t ldc, int n_limbs) {
-  int rc = check_ozi_args(m, n, k, A, lda, B, ldb, n_limbs);
-  if (rc) return rc;
-  if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
-  if (m == 0 || n == 0) return OZFP4_OK;
-  if (!C) return OZFP4_EINVAL;
-  if (k == 0) {
-    DeviceState* d;
-    rc = device_state(&d);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_fill_f64_matrix, dim3(stride_blocks(m * n, 256)), dim3(256), 0, g_stream, C,
-                       m, n, ldc);
-    HIP_TRY(hipGetLastError());
-    return OZFP4_OK;
-  }
-  OziPlan p;
-  DeviceState* d;
-  rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
-  if (rc) return rc;
-  rc = run_ozi(p, d, A, lda, B, ldb, C, ldc, 4, start_flag(d), nullptr, nullptr);
-  if (rc) return rc;
-  return finish_with_flag(d, 5);
+  return dgemm_ozi_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_limbs);
 }
 
 int ozfp4_ozi_config(int n_limbs, int32_t* capacity, int32_t* n_planes, int32_t* n_groups) {
@@ -1034,7 +1118,7 @@ int ozfp4_ozi_config(int n_limbs, int32_t* capacity, int32_t* n_planes, int32_t*
 int ozfp4_ozi_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                           const double* B, int64_t ldb, int n_limbs, uint8_t* planes_a,
                           uint8_t* planes_b) {
-  int rc = check_ozi_args(m, n, k, A, lda, B, ldb, n_limbs);
+  int rc = check_ozi_args(m, n, k, A, B, leading_ok(m, k, lda, ldb), n_limbs);
   if (rc) return rc;
   if (m == 0 || n == 0 || k == 0) return OZFP4_EINVAL;
   if (!planes_a || !planes_b) return OZFP4_EINVAL;
@@ -1042,14 +1126,14 @@ int ozfp4_ozi_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int6
   DeviceState* d;
   rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
   if (rc) return rc;
-  rc = run_ozi(p, d, A, lda, B, ldb, nullptr, 0, 2, start_flag(d), planes_a, planes_b);
+  rc = run_ozi(p, d, Mat{A, 1, lda}, Mat{B, 1, ldb}, nullptr, 0, 2, start_flag(d), planes_a, planes_b);
   if (rc) return rc;
   return finish_with_flag(d, 0);
 }
 
 int ozfp4_ozi_partials(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                        const double* B, int64_t ldb, int n_limbs, int64_t* H, int64_t ldh) {
-  int rc = check_ozi_args(m, n, k, A, lda, B, ldb, n_limbs);
+  int rc = check_ozi_args(m, n, k, A, B, leading_ok(m, k, lda, ldb), n_limbs);
   if (rc) return rc;
   if (m == 0 || n == 0 || k == 0) return OZFP4_EINVAL;
   if (!H || ldh < m) return OZFP4_EINVAL;
@@ -1057,7 +1141,7 @@ int ozfp4_ozi_partials(int64_t m, int64_t n, int64_t k, const double* A, int64_t
   DeviceState* d;
   rc = prepare_ozi(m, n, k, n_limbs, &p, &d);
   if (rc) return rc;
-  rc = run_ozi(p, d, A, lda, B, ldb, nullptr, 0, 3, start_flag(d), nullptr, nullptr);
+  rc = run_ozi(p, d, Mat{A, 1, lda}, Mat{B, 1, ldb}, nullptr, 0, 3, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
   for (int h = 0; h < p.nh; ++h) {
     HIP_TRY(hipMemcpy2DAsync(H + (size_t)h * ldh * n, (size_t)ldh * sizeof(int64_t),
@@ -1199,7 +1283,7 @@ int ozfp4_plane_layout(int64_t lines, int64_t k, int64_t* rows_pad, int64_t* k_p
 
 int ozfp4_scales(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                  int64_t ldb, int n_moduli, int32_t* s, int32_t* t) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
+  int rc = check_dgemm_args(m, n, k, A, B, leading_ok(m, k, lda, ldb), n_moduli);
   if (rc) return rc;
   if (m == 0 || n == 0 || k == 0) return OZFP4_EINVAL;
   if (!s || !t) return OZFP4_EINVAL;
@@ -1207,10 +1291,11 @@ int ozfp4_scales(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, 
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 0, start_flag(d), nullptr, nullptr);
+  rc = run_dgemm(p, d, Mat{A, 1, lda}, Mat{B, 1, ldb}, nullptr, 0, 0, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
   ConvOperand a, b;
-  conv_operands(p, A, lda, B, ldb, p.cA, p.cB, d->ws, nullptr, nullptr, p.off_r, &a, &b);
+  conv_operands(p, Mat{A, 1, lda}, Mat{B, 1, ldb}, p.cA, p.cB, d->ws, nullptr, nullptr, p.off_r, &a,
+                &b);
   HIP_TRY(launch_shifts(g_stream, a, s));
   HIP_TRY(launch_shifts(g_stream, b, t));
   return finish_with_flag(d, 0);
@@ -1219,7 +1304,7 @@ int ozfp4_scales(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, 
 int ozfp4_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                       const double* B, int64_t ldb, int n_moduli, uint8_t* planes_a,
                       uint8_t* planes_b) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
+  int rc = check_dgemm_args(m, n, k, A, B, leading_ok(m, k, lda, ldb), n_moduli);
   if (rc) return rc;
   if (m == 0 || n == 0 || k == 0) return OZFP4_EINVAL;
   if (!planes_a || !planes_b) return OZFP4_EINVAL;
@@ -1227,14 +1312,14 @@ int ozfp4_limb_planes(int64_t m, int64_t n, int64_t k, const double* A, int64_t 
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 2, start_flag(d), planes_a, planes_b);
+  rc = run_dgemm(p, d, Mat{A, 1, lda}, Mat{B, 1, ldb}, nullptr, 0, 2, start_flag(d), planes_a, planes_b);
   if (rc) return rc;
   return finish_with_flag(d, 0);
 }
 
 int ozfp4_residues(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda, const double* B,
                    int64_t ldb, int n_moduli, uint8_t* R, int64_t ldr) {
-  int rc = check_dgemm_args(m, n, k, A, lda, B, ldb, n_moduli);
+  int rc = check_dgemm_args(m, n, k, A, B, leading_ok(m, k, lda, ldb), n_moduli);
   if (rc) return rc;
   if (m == 0 || n == 0 || k == 0) return OZFP4_EINVAL;
   if (!R || ldr < m) return OZFP4_EINVAL;
@@ -1242,7 +1327,7 @@ int ozfp4_residues(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda
   DeviceState* d;
   rc = prepare(m, n, k, n_moduli, &p, &d);
   if (rc) return rc;
-  rc = run_dgemm(p, d, A, lda, B, ldb, nullptr, 0, 3, start_flag(d), nullptr, nullptr);
+  rc = run_dgemm(p, d, Mat{A, 1, lda}, Mat{B, 1, ldb}, nullptr, 0, 3, start_flag(d), nullptr, nullptr);
   if (rc) return rc;
   for (int l = 0; l < n_moduli; ++l) {
     HIP_TRY(hipMemcpy2DAsync(R + (size_t)l * ldr * n, (size_t)ldr,

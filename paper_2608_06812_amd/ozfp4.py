@@ -7,9 +7,12 @@ torch, pass device pointers and the current torch stream, and raise on a
 nonzero status. Every arithmetic step runs in the library's HIP kernels;
 there is no CPU fallback, and ``load()`` raises if the library is missing.
 
-Matrices are column-major as in BLAS: a torch tensor X of shape (rows, cols)
-is accepted when X.stride(0) == 1, with leading dimension X.stride(1).
-``colmajor(X)`` makes such a copy of any 2-D tensor.
+The C entry points take column-major matrices as in BLAS (a torch tensor X of
+shape (rows, cols) with X.stride(0) == 1 and leading dimension X.stride(1));
+the products also take row-major ones (X.stride(1) == 1) as they are, through
+ozfp4_product. ``colmajor(X)`` makes a column-major copy of any 2-D tensor;
+the helpers do so for every other layout, and for row-major inputs of the
+parity hooks.
 """
 
 from __future__ import annotations
@@ -36,6 +39,8 @@ OZFP4_MAX_K_S8 = 16777216
 OZFP4_MAX_ELEMENTS = 1 << 48
 OZFP4_OZI_MAX_LIMBS = 15
 OZFP4_SCRATCH_BYTES = 268435456
+(OZFP4_OP_DGEMM, OZFP4_OP_DGEMM_NOALLOC, OZFP4_OP_DGEMM_SPLIT, OZFP4_OP_DGEMM_OZI, OZFP4_OP_SGEMM,
+ OZFP4_OP_IGEMM_S8) = range(6)
 
 _lib = None
 
@@ -46,6 +51,7 @@ _SIGNATURES = {
     "ozfp4_init": (_int, []),
     "ozfp4_dgemm_split": (_int, [_i64, _i64, _i64, _p, _i64, _p, _i64, _p, _i64, _int]),
     "ozfp4_dgemm_noalloc": (_int, [_i64, _i64, _i64, _p, _i64, _p, _i64, _p, _i64, _int]),
+    "ozfp4_product": (_int, [_int, _i64, _i64, _i64, _p, _i64, _i64, _p, _i64, _i64, _p, _i64, _int]),
     "ozfp4_set_stream": (_int, [_p]),
     "ozfp4_finalize": (_int, []),
     "ozfp4_strerror": (ctypes.c_char_p, [_int]),
@@ -117,6 +123,10 @@ def ozfp4_dgemm_noalloc(m, n, k, A, lda, B, ldb, C, ldc, n_moduli) -> int:
 
 def ozfp4_igemm_s8(m, n, k, A, lda, B, ldb, C, ldc) -> int:
     return load().ozfp4_igemm_s8(m, n, k, A, lda, B, ldb, C, ldc)
+
+
+def ozfp4_product(op, m, n, k, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, count) -> int:
+    return load().ozfp4_product(op, m, n, k, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, count)
 
 
 def ozfp4_set_stream(stream) -> int:
@@ -264,7 +274,7 @@ def colmajor(X):
     return X.t().contiguous().t()
 
 
-def _cm(X, dtype, name):
+def _check_operand(X, dtype, name):
     import torch
     if not isinstance(X, torch.Tensor) or X.dim() != 2:
         raise TypeError(f"{name} must be a 2-D torch tensor")
@@ -272,10 +282,44 @@ def _cm(X, dtype, name):
         raise TypeError(f"{name} must be {dtype}")
     if not X.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
+
+
+def _cm(X, dtype, name):
+    _check_operand(X, dtype, name)
     if X.stride(0) != 1 and X.shape[0] > 1:
         X = colmajor(X)
     ld = max(1, X.stride(1) if X.shape[1] > 1 else X.shape[0])
     return X, ld
+
+
+def _strided(X, dtype, name):
+    """X, its row stride and its column stride for ozfp4_product: row-major
+    tensors as they are, any other layout as _cm takes it."""
+    _check_operand(X, dtype, name)
+    rows, cols = X.shape
+    if rows > 1 and cols > 1 and X.stride(0) != 1 and X.stride(1) == 1 and X.stride(0) >= cols:
+        return X, X.stride(0), 1
+    X, ld = _cm(X, dtype, name)
+    return X, 1, ld
+
+
+def _product(op, A, B, in_dtype, out_dtype, count, out, where):
+    """C = A B by the entry point `op` into `out`, or a new column-major
+    tensor; returns C."""
+    A, a_rs, a_cs = _strided(A, in_dtype, "A")
+    B, b_rs, b_cs = _strided(B, in_dtype, "B")
+    m, k = A.shape
+    k2, n = B.shape
+    if k != k2:
+        raise ValueError("inner dimensions differ")
+    C = _empty_cm(m, n, out_dtype, A.device) if out is None else out
+    if C.shape != (m, n) or C.dtype != out_dtype or (C.stride(0) != 1 and m > 1):
+        raise ValueError(f"out must be a column-major {str(out_dtype).split('.')[-1]} (m x n) tensor")
+    ldc = max(1, C.stride(1) if n > 1 else m)
+    with _on(A.device, B, C):
+        _check(ozfp4_product(op, m, n, k, A.data_ptr(), a_rs, a_cs, B.data_ptr(), b_rs, b_cs,
+                             C.data_ptr(), ldc, count), where)
+    return C
 
 
 @contextlib.contextmanager
@@ -301,20 +345,7 @@ def dgemm(A, B, n_moduli: int = 19, out=None):
     """C = fl(A B) for float64 device tensors A (m x k), B (k x n) by Ozaki
     scheme II on FP4 limbs; returns C (m x n), column-major."""
     import torch
-    A, lda = _cm(A, torch.float64, "A")
-    B, ldb = _cm(B, torch.float64, "B")
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ")
-    C = _empty_cm(m, n, torch.float64, A.device) if out is None else out
-    if C.shape != (m, n) or C.dtype != torch.float64 or (C.stride(0) != 1 and m > 1):
-        raise ValueError("out must be a column-major float64 (m x n) tensor")
-    ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_dgemm(m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, n_moduli),
-               "ozfp4_dgemm")
-    return C
+    return _product(OZFP4_OP_DGEMM, A, B, torch.float64, torch.float64, n_moduli, out, "ozfp4_dgemm")
 
 
 def dgemm_split(A, B, n_moduli: int = 19, out=None):
@@ -322,20 +353,8 @@ def dgemm_split(A, B, n_moduli: int = 19, out=None):
     split of the converted operands (ozfp4_dgemm_split); returns C (m x n),
     column-major."""
     import torch
-    A, lda = _cm(A, torch.float64, "A")
-    B, ldb = _cm(B, torch.float64, "B")
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ")
-    C = _empty_cm(m, n, torch.float64, A.device) if out is None else out
-    if C.shape != (m, n) or C.dtype != torch.float64 or (C.stride(0) != 1 and m > 1):
-        raise ValueError("out must be a column-major float64 (m x n) tensor")
-    ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_dgemm_split(m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc,
-                                 n_moduli), "ozfp4_dgemm_split")
-    return C
+    return _product(OZFP4_OP_DGEMM_SPLIT, A, B, torch.float64, torch.float64, n_moduli, out,
+                    "ozfp4_dgemm_split")
 
 
 def dgemm_noalloc(A, B, out, n_moduli: int = 19):
@@ -343,41 +362,17 @@ def dgemm_noalloc(A, B, out, n_moduli: int = 19):
     `out` (m x n): the library allocates nothing; the current device must
     have been set up (ozfp4_init)."""
     import torch
-    A, lda = _cm(A, torch.float64, "A")
-    B, ldb = _cm(B, torch.float64, "B")
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ")
-    C = out
-    if not isinstance(C, torch.Tensor) or C.shape != (m, n) or C.dtype != torch.float64 or \
-            (C.stride(0) != 1 and m > 1):
+    if not isinstance(out, torch.Tensor):
         raise ValueError("out must be a column-major float64 (m x n) tensor")
-    ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_dgemm_noalloc(m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc,
-                                   n_moduli), "ozfp4_dgemm_noalloc")
-    return C
+    return _product(OZFP4_OP_DGEMM_NOALLOC, A, B, torch.float64, torch.float64, n_moduli, out,
+                    "ozfp4_dgemm_noalloc")
 
 
 def igemm_s8(A, B, out=None):
     """C = A B for int8 device tensors, int32 result wrapping modulo 2^32;
     returns C (m x n), column-major."""
     import torch
-    A, lda = _cm(A, torch.int8, "A")
-    B, ldb = _cm(B, torch.int8, "B")
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ")
-    C = _empty_cm(m, n, torch.int32, A.device) if out is None else out
-    if C.shape != (m, n) or C.dtype != torch.int32 or (C.stride(0) != 1 and m > 1):
-        raise ValueError("out must be a column-major int32 (m x n) tensor")
-    ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_igemm_s8(m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc),
-               "ozfp4_igemm_s8")
-    return C
+    return _product(OZFP4_OP_IGEMM_S8, A, B, torch.int8, torch.int32, 0, out, "ozfp4_igemm_s8")
 
 
 def scales(A, B, n_moduli: int = 19):
@@ -435,20 +430,8 @@ def dgemm_ozi(A, B, n_limbs: int = OZFP4_OZI_MAX_LIMBS, out=None):
     scheme I on FP4 limbs with n_limbs limbs per operand; returns C (m x n),
     column-major."""
     import torch
-    A, lda = _cm(A, torch.float64, "A")
-    B, ldb = _cm(B, torch.float64, "B")
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ")
-    C = _empty_cm(m, n, torch.float64, A.device) if out is None else out
-    if C.shape != (m, n) or C.dtype != torch.float64 or (C.stride(0) != 1 and m > 1):
-        raise ValueError("out must be a column-major float64 (m x n) tensor")
-    ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_dgemm_ozi(m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc,
-                               n_limbs), "ozfp4_dgemm_ozi")
-    return C
+    return _product(OZFP4_OP_DGEMM_OZI, A, B, torch.float64, torch.float64, n_limbs, out,
+                    "ozfp4_dgemm_ozi")
 
 
 def ozi_limb_planes(A, B, n_limbs: int = OZFP4_OZI_MAX_LIMBS):
@@ -503,22 +486,10 @@ def sgemm(A, B, n_moduli: int | None = None, out=None):
     scheme II on FP4 limbs; n_moduli defaults to the fewest moduli with
     24-bit capacities for this k. Returns C (m x n), column-major."""
     import torch
-    A, lda = _cm(A, torch.float32, "A")
-    B, ldb = _cm(B, torch.float32, "B")
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ")
-    if n_moduli is None:
-        n_moduli = sgemm_moduli(max(1, k))
-    C = _empty_cm(m, n, torch.float32, A.device) if out is None else out
-    if C.shape != (m, n) or C.dtype != torch.float32 or (C.stride(0) != 1 and m > 1):
-        raise ValueError("out must be a column-major float32 (m x n) tensor")
-    ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_sgemm(m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, n_moduli),
-               "ozfp4_sgemm")
-    return C
+    # 0 is the library's own choice (that of sgemm_moduli); a caller's 0 stays
+    # the error that any count below 2 is
+    count = 0 if n_moduli is None else (n_moduli or 1)
+    return _product(OZFP4_OP_SGEMM, A, B, torch.float32, torch.float32, count, out, "ozfp4_sgemm")
 
 
 # ------------------------------------------------------- reference measurements
