@@ -149,11 +149,13 @@ hipError_t launch_line_max(hipStream_t stream, bool f32, const ConvOperand& a,
 hipError_t launch_encode(hipStream_t stream, bool f32, const ConvOperand& a, const ConvOperand& b,
                          int L, const ModConst& mod, const ModConst* mc, const uint16_t* lut,
                          int terms, int d2) {
-  if (f32) return launch_encode_kernel<false, false, float>(stream, a, b, L, mod, mc, lut, terms, d2);
+  if (f32) return launch_encode_kernel<false, false, float>(stream, a, b, L, mod, mc, lut, 0);
+  // the two-term split keeps to 53 bits
+  if (terms == 2)
+    return launch_encode_kernel<false, false, double, 2>(stream, a, b, L, mod, mc, lut, d2);
   // c_A >= c_B, so the wide encoder is exact for both where A needs it
-  if (a.cap > 53)
-    return launch_encode_kernel<false, true, double>(stream, a, b, L, mod, mc, lut, terms, d2);
-  return launch_encode_kernel<false, false, double>(stream, a, b, L, mod, mc, lut, terms, d2);
+  if (a.cap > 53) return launch_encode_kernel<false, true, double>(stream, a, b, L, mod, mc, lut, 0);
+  return launch_encode_kernel<false, false, double>(stream, a, b, L, mod, mc, lut, 0);
 }
 
 hipError_t launch_shifts(hipStream_t stream, const ConvOperand& op, int32_t* out) {

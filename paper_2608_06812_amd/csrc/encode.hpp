@@ -16,17 +16,25 @@ namespace ozfp4 {
 // each plane of that modulus: c0 (plane 2l), c1 (plane 2l + 1) and, in the
 // Karatsuba mode (kKar) for a Karatsuba modulus, c0 + c1 (plane
 // 2L + ksum).
-//   x = round_half_even(X * 2^s), |x| <= 2^53, is exact in FP64 and kept as
-//   E x, E = the table entry size in bytes (2, or 4 in the Karatsuba mode).
-//   For each m, q = floor(E x * fl(1/m) / E) is within one of floor(x / m),
-//   so E r = E x - q E m (exact FMA) has r in [-m, 2m), and r indexes a
-//   table over [-m, 2m) that maps every estimate to the codes of its class.
-//   Adding 2^52 plus the table's byte offset to E r gives a double in
-//   [2^52, 2^53) whose low 32 bits are the LDS byte address of the entry.
+//   x = round_half_even(X * 2^s), |x| <= 2^53, is exact in FP64. For each m,
+//   q = rint(x fl(1/m)) is within 0.7 of x / m, so r = x - q m lies in
+//   (-m, m) and indexes a table over [-m, 2m) that maps every estimate to the
+//   codes of its class (E bytes an entry: 2, or 4 in the Karatsuba mode).
+//   Only the LDS byte address of the entry, E r + zero below 2^16, is formed,
+//   and modulo 2^16: one FMA adds x fl(1/m) to 1.5 * 2^52 + q0, whose low
+//   bits then hold q + q0, and one 16-bit multiply-add gives
+//   E x - (q + q0) E m with E x modulo 2^16 kept from the conversion; q0 is
+//   chosen so that -q0 E m is the address `zero` of remainder 0. (An even
+//   m = odd 2^z needs zero / E divisible by 2^z: tables start at multiples of
+//   16 entries, and m <= 169 has z <= 4.)
+//   Two VALU operations a value and modulus before the lookup, in place of
+//   four in FP64: both operands at 2048^3 67 -> 61 us (18 moduli), 1500 x 3001
+//   44.6 -> 38.2 us, FP32 2048^3 48 -> 43 us. Large operands are bound by
+//   their plane writes (26 B a value at 18 moduli, 4.2-4.9 TB/s).
 //   kWide (capacity above 53 bits): x = A 2^s is an exact double below
-//   2^63; the same floor step first brings E x down to an exact E d with
-//   |d| < 2^15 (the quotient is within 2^8 of floor(x / m), and the FMA's
-//   result is representable, so exact), and the step above then runs on d.
+//   2^63; a floor step first brings x down to an exact d with |d| < 2^15 (the
+//   quotient is within 2^8 of floor(x / m), and the FMA's result is
+//   representable, so exact), and the step above then runs on d.
 //   Second term (the two-term split, blockIdx.z == 1): the value encoded is
 //   x2 = round_half_even((A 2^s - x) 2^d2), |x2| <= 2^(d2 - 1); A 2^s - x
 //   is exact (the fraction of A 2^s), and so is its product by 2^d2.
@@ -34,17 +42,33 @@ namespace ozfp4 {
 // One launch covers both operands (blocks below blocks_a encode a, the rest
 // b), blockIdx.y the moduli per_group * y .. + per_group - 1.
 template <typename T>
-__device__ __forceinline__ uint32_t lut_lookup(double y) {
-  const uint32_t addr = (uint32_t)__double_as_longlong(y);
+__device__ __forceinline__ uint32_t lut_lookup(uint32_t addr) {
   return *reinterpret_cast<__attribute__((address_space(3))) const T*>((size_t)addr);
 }
 
-template <bool kKar, bool kWide, typename TIn = double>
+// The integer x modulo 2^32, |x| <= 2^53.
+__device__ __forceinline__ uint32_t low_word(double x) {
+  const double lo = __builtin_fma(-0x1p32, __builtin_rint(x * 0x1p-32), x);   // |lo| <= 2^31
+  return (uint32_t)__double_as_longlong(lo + 0x1.8p52);
+}
+
+template <bool kWide>
+__device__ __forceinline__ uint32_t entry_address(double x, uint16_t xl, double inv, double md,
+                                                  double magic, uint16_t step, uint32_t e) {
+  if constexpr (kWide) {
+    x = __builtin_fma(-__builtin_floor(x * inv), md, x);
+    xl = (uint16_t)(e * (uint32_t)__double_as_longlong(x + 0x1.8p52));
+  }
+  const uint16_t q = (uint16_t)__double_as_longlong(__builtin_fma(x, inv, magic));
+  return (uint16_t)(q * step + xl);
+}
+
+template <bool kKar, bool kWide, typename TIn, int kTerms>
 __global__ __launch_bounds__(256) void k_encode_dgemm(
     ConvOperand a, ConvOperand b, uint32_t blocks_a, int L, int per_group,
     const ModConst* __restrict__ mc, const void* __restrict__ lut, int d2) {
   typedef typename std::conditional<kKar, uint32_t, uint16_t>::type Entry;
-  constexpr double kE = (double)sizeof(Entry);
+  constexpr uint32_t kE = (uint32_t)sizeof(Entry);
   extern __shared__ __attribute__((aligned(16))) uint8_t s_raw[];
   const bool is_b = blockIdx.x >= blocks_a;
   const uint32_t block = is_b ? blockIdx.x - blocks_a : blockIdx.x;
@@ -54,7 +78,7 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
   const int64_t plane_bytes = op.plane_bytes;
   const TIn* X = reinterpret_cast<const TIn*>(op.X);
   const int l0 = (int)blockIdx.y * per_group, l1 = min(L, l0 + per_group);
-  const bool second = blockIdx.z != 0;
+  const bool second = kTerms == 2 && blockIdx.z != 0;
   uint8_t* planes = op.planes + (second ? op.term_bytes : 0);
   // this group's table, copied in 32-bit words from the word that holds its
   // first entry
@@ -107,22 +131,31 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
         src += ks;
       }
     }
+    uint16_t xl[32];   // E x modulo 2^16
 #pragma unroll
     for (int e = 0; e < 32; ++e) {
       const double T = __builtin_ldexp(xe[e], s);
       double t = __builtin_rint(T);
-      if (second) t = __builtin_rint(__builtin_ldexp(T - t, d2));
+      if constexpr (kTerms == 2) {
+        if (second) t = __builtin_rint(__builtin_ldexp(T - t, d2));
+      }
       // finite inputs give |t| <= 2^53 (2^63 when wide); NaN/Inf (reported
       // by the scale stage) must not drive the table address out of range
-      xe[e] = (__builtin_fabs(t) <= (kWide ? 0x1p63 : 0x1p53)) ? kE * t : 0.0;
+      t = (__builtin_fabs(t) <= (kWide ? 0x1p63 : 0x1p53)) ? t : 0.0;
+      xe[e] = t;
+      if constexpr (!kWide) xl[e] = (uint16_t)(kE * low_word(t));
     }
     uint8_t* out = planes + ((int64_t)rb * kblocks + kb) * kFragBytes + lane * 16;
     for (int l = l0; l < l1; ++l) {
       const int m = mc->m[l];
-      const double inv = mc->inv[l] / kE;
-      const double mE = kE * mc->md[l];
-      const double base =
-          0x1p52 + (double)(lds_base + (uint32_t)kE * (uint32_t)(mc->lut_off[l] - word0 * kPerWord + m));
+      const double inv = mc->inv[l], md = mc->md[l];
+      // LDS address of the table entry of remainder 0, and the offset q0 of
+      // the quotients with q0 E m = -address modulo 2^16
+      const uint32_t zero = lds_base + kE * (uint32_t)(mc->lut_off[l] - word0 * kPerWord + m);
+      const uint32_t q0 =
+          ((uint32_t)(-(int)(zero / kE)) >> mc->twos[l]) * (uint32_t)mc->odd_inv[l] & (0xffffu / kE);
+      const double magic = 0x1.8p52 + (double)q0;
+      const uint16_t step = (uint16_t)(0u - kE * (uint32_t)m);
       uint32_t w0[4], w1[4], w2[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -130,15 +163,10 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
           const int e = g * 8 + h * 2;
-          double x0 = xe[e], x1 = xe[e + 1];
-          if constexpr (kWide) {
-            x0 = __builtin_fma(-__builtin_floor(x0 * inv), mE, x0);
-            x1 = __builtin_fma(-__builtin_floor(x1 * inv), mE, x1);
-          }
-          const double q0 = __builtin_floor(x0 * inv);
-          const double q1 = __builtin_floor(x1 * inv);
-          const uint32_t E0 = lut_lookup<Entry>(__builtin_fma(-q0, mE, x0) + base);
-          const uint32_t E1 = lut_lookup<Entry>(__builtin_fma(-q1, mE, x1) + base);
+          const uint32_t E0 = lut_lookup<Entry>(
+              entry_address<kWide>(xe[e], kWide ? 0 : xl[e], inv, md, magic, step, kE));
+          const uint32_t E1 = lut_lookup<Entry>(
+              entry_address<kWide>(xe[e + 1], kWide ? 0 : xl[e + 1], inv, md, magic, step, kE));
           // byte 0: plane-0 byte, byte 1: plane-1 byte (byte 2: sum plane)
           p[h] = E0 | (E1 << 4);
         }
@@ -184,13 +212,13 @@ inline int moduli_per_group(const ConvOperand& a, const ConvOperand& b, int L, i
 }
 
 // Launches the encoder over both operands. `mod` is the host copy of mc;
-// terms: 2 for the two-term split.
-template <bool kKar, bool kWide, typename TIn>
+// kTerms: 2 for the two-term split.
+template <bool kKar, bool kWide, typename TIn, int kTerms = 1>
 hipError_t launch_encode_kernel(hipStream_t stream, const ConvOperand& a, const ConvOperand& b,
                                 int L, const ModConst& mod, const ModConst* mc, const void* lut,
-                                int terms, int d2) {
+                                int d2) {
   const uint32_t ba = encode_blocks(a), bb = encode_blocks(b);
-  const int per_group = moduli_per_group(a, b, L, terms);
+  const int per_group = moduli_per_group(a, b, L, kTerms);
   const int groups = (L + per_group - 1) / per_group;
   const size_t entry = kKar ? sizeof(uint32_t) : sizeof(uint16_t);
   size_t lds = 0;
@@ -198,7 +226,7 @@ hipError_t launch_encode_kernel(hipStream_t stream, const ConvOperand& a, const 
     const int l0 = g * per_group, l1 = std::min(L, l0 + per_group) - 1;
     lds = std::max(lds, entry * (size_t)(mod.lut_off[l1] + 3 * mod.m[l1] - mod.lut_off[l0]) + 8);
   }
-  hipLaunchKernelGGL((k_encode_dgemm<kKar, kWide, TIn>), dim3(ba + bb, groups, terms), dim3(256),
+  hipLaunchKernelGGL((k_encode_dgemm<kKar, kWide, TIn, kTerms>), dim3(ba + bb, groups, kTerms), dim3(256),
                      lds, stream, a, b, ba, L, per_group, mc, lut, d2);
   return hipGetLastError();
 }

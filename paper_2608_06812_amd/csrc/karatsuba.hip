@@ -238,8 +238,8 @@ __global__ __launch_bounds__(512, 1) void k_gemm_res_kar(
 hipError_t launch_encode_kar(hipStream_t stream, const ConvOperand& a, const ConvOperand& b, int L,
                              const ModConst& mod, const ModConst* mc, const uint32_t* lut) {
   if (a.cap > 53)
-    return launch_encode_kernel<true, true, double>(stream, a, b, L, mod, mc, lut, 1, 0);
-  return launch_encode_kernel<true, false, double>(stream, a, b, L, mod, mc, lut, 1, 0);
+    return launch_encode_kernel<true, true, double>(stream, a, b, L, mod, mc, lut, 0);
+  return launch_encode_kernel<true, false, double>(stream, a, b, L, mod, mc, lut, 0);
 }
 
 hipError_t launch_gemm_res_kar(unsigned grid, hipStream_t stream, const uint8_t* PA,

@@ -225,7 +225,9 @@ inline bool one_limb_split(int r, int m, int* c) {
 struct ModConst {
   int m[kMaxModuli];
   int ksum[kMaxModuli];      // index among the Karatsuba moduli of the list, or -1
-  int lut_off[kMaxModuli];   // start of modulus l in the encoder LUT (entries)
+  int lut_off[kMaxModuli];   // start of modulus l in the encoder LUT (entries, a multiple of 16)
+  int odd_inv[kMaxModuli];   // inverse of m's odd part modulo 2^16
+  int twos[kMaxModuli];      // m = odd part * 2^twos, twos <= 4
   double inv[kMaxModuli];    // fl(1 / m)
   double md[kMaxModuli];     // m as double
 };
@@ -307,6 +309,23 @@ inline bool build_crt(const std::vector<int>& moduli, CrtConst* crt, Big* P) {
   return true;
 }
 
+// The fields of entry i of a constant block that follow from its modulus.
+inline void set_modulus(ModConst& mc, int i, int m, int lut_off) {
+  mc.m[i] = m;
+  mc.lut_off[i] = lut_off;
+  mc.inv[i] = 1.0 / (double)m;
+  mc.md[i] = (double)m;
+  int twos = 0, odd = m;
+  while ((odd & 1) == 0) { odd >>= 1; ++twos; }
+  uint32_t x = (uint32_t)odd;                             // Newton: x odd = 1 mod 2^3,
+  for (int it = 0; it < 4; ++it) x *= 2u - (uint32_t)odd * x;   // 6, 12, 24, 48 bits
+  mc.odd_inv[i] = (int)(x & 0xffffu);
+  mc.twos[i] = twos;
+}
+
+// Start of the next modulus in an encoder LUT of n entries.
+inline int lut_align(int n) { return (n + 15) & ~15; }
+
 // Encoder LUT of modulus m: 3m entries, index r + m for a remainder
 // estimate r in [-m, 2m) of a signed integer x; entry = code(c0) |
 // code(c1) << 8 for the canonical split of the class of x mod m. The LUT of
@@ -324,12 +343,9 @@ inline bool build_tables(HostTables& T) {
   for (int l = 0; l < kMaxModuli; ++l) {
     int m = T.moduli[l];
     const bool kar = is_karatsuba(m);
-    T.mod.m[l] = m;
+    set_modulus(T.mod, l, m, off);
     T.mod.ksum[l] = kar ? nk++ : -1;
     T.nk[l + 1] = nk;
-    T.mod.lut_off[l] = off;
-    T.mod.inv[l] = 1.0 / (double)m;
-    T.mod.md[l] = (double)m;
     for (int ri = -m; ri < 2 * m; ++ri) {
       int cls = ((ri % m) + m) % m;
       int c0, c1;
@@ -346,7 +362,9 @@ inline bool build_tables(HostTables& T) {
       if (k0 < 0 || k1 < 0 || ks < 0) return false;
       T.lut_k.push_back((uint32_t)k0 | ((uint32_t)k1 << 8) | ((uint32_t)ks << 16));
     }
-    off += 3 * m;
+    off = lut_align(off + 3 * m);
+    T.lut.resize(off);
+    T.lut_k.resize(off);
   }
   // int8: three greedy limbs (X_3 = 732 >= 128)
   for (int v = -128; v < 128; ++v) {
@@ -380,11 +398,8 @@ inline bool build_tables(HostTables& T) {
       const int pl = l < h ? l : l - h;
       for (ModConst* mc : {&Ls.mod, &part}) {
         const int i = mc == &Ls.mod ? l : pl;
-        mc->m[i] = m;
+        set_modulus(*mc, i, m, off1);
         mc->ksum[i] = -1;
-        mc->lut_off[i] = off1;
-        mc->inv[i] = 1.0 / (double)m;
-        mc->md[i] = (double)m;
       }
       for (int ri = -m; ri < 2 * m; ++ri) {
         const int cls = ((ri % m) + m) % m;
@@ -398,7 +413,8 @@ inline bool build_tables(HostTables& T) {
         if (k0 < 0 || k1 < 0) return false;
         Ls.lut.push_back((uint16_t)(k0 | (k1 << 8)));
       }
-      off1 += 3 * m;
+      off1 = lut_align(off1 + 3 * m);
+      Ls.lut.resize(off1);
     }
     if (!build_crt(Ls.moduli, Ls.crt, Ls.P)) return false;
   }
