@@ -19,7 +19,11 @@ namespace {
 // X 2^-(s + t + 2d) once. The residues of X12 arrive as two sets (A1 B2 and
 // A2 B1 from two GEMMs); their sum is reduced once more modulo m, so every
 // r_l is below m_l as the exactness of the chunk sums requires. t0 is the
-// first thread index of the launch.
+// first thread index of the launch. Bound by integer VALU work (three exact
+// symmetric integers and 256-bit additions an element) and, at small sizes,
+// by its chain; with one load at a time it waited for 4 L of them: 126 -> 101
+// us at 1536 x 1536, 33 -> 22 us at 256 x 256 (19 moduli). One or two rows a
+// thread take 245 and 382 us at 1536 x 1536 (sub-word loads).
 template <int NC>
 __global__ __launch_bounds__(256) void k_crt_split(
     const uint8_t* __restrict__ R11, const uint8_t* __restrict__ R12a,
@@ -47,22 +51,30 @@ __global__ __launch_bounds__(256) void k_crt_split(
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int c = 0; c < NC; ++c) sig[e][c] = 0.0;
-    for (int l = 0; l < L; ++l) {
-      uint32_t w;
+    // all loads of a product first, so that they are in flight together
+    uint32_t words[kMaxModuli], words2[kMaxModuli];
+    const uint8_t* src = (p == 0 ? R11 : (p == 1 ? R12a : R22)) + off;
+#pragma unroll
+    for (int l = 0; l < kMaxModuli; ++l)
+      if (l < L) {
+        words[l] = *reinterpret_cast<const uint32_t*>(src + (int64_t)l * rplane);
+        if (p == 1) words2[l] = *reinterpret_cast<const uint32_t*>(R12b + (int64_t)l * rplane + off);
+      }
+#pragma unroll
+    for (int l = 0; l < kMaxModuli; ++l) {
+      if (l >= L) break;
+      uint32_t w = words[l];
       if (p == 1) {
         // per byte: (a + b) mod m with a, b < m
-        const uint32_t a = *reinterpret_cast<const uint32_t*>(R12a + l * rplane + off);
-        const uint32_t b = *reinterpret_cast<const uint32_t*>(R12b + l * rplane + off);
+        const uint32_t a = w, b = words2[l];
         const uint32_t mm = (uint32_t)mc->m[l];
         w = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           uint32_t r = ((a >> (8 * e)) & 0xffu) + ((b >> (8 * e)) & 0xffu);
-          r -= (r >= mm) ? mm : 0u;
+          r = min(r, r - mm);   // r - m wraps above r where r < m
           w |= r << (8 * e);
         }
-      } else {
-        w = *reinterpret_cast<const uint32_t*>((p == 0 ? R11 : R22) + l * rplane + off);
       }
       double W[NC];
 #pragma unroll
