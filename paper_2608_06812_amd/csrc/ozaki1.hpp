@@ -8,9 +8,10 @@
 
 namespace ozfp4 {
 
-// k_encode_ozi: nplanes greedy limb planes of the lines of both operands
+// k_encode_ozi: nplanes (a multiple of 3) greedy limb planes of the lines of
+// both operands; lut13 as HostTables::lut13, in device memory
 hipError_t launch_encode_ozi(hipStream_t stream, const ConvOperand& a, const ConvOperand& b,
-                             int nplanes);
+                             int nplanes, const uint32_t* lut13);
 
 // k_gemm_ozi over every 128 x 128 tile of every block anti-diagonal; H holds
 // 2 nblk - 1 planes of m_pad x n_pad int64 (column-major, ld m_pad)

@@ -43,6 +43,7 @@ struct DeviceState {
   uint16_t* d_lut = nullptr;
   uint32_t* d_lut_k = nullptr;   // encoder LUT of the Karatsuba mode
   uint16_t* d_lut8 = nullptr;
+  uint32_t* d_lut13 = nullptr;   // scheme-I encoder table
   struct List {                 // a list with one-limb heads (index h)
     ModConst* mod = nullptr;
     ModConst* tail = nullptr;
@@ -99,6 +100,7 @@ void release_device(DeviceState& d) {
   (void)hipFree(d.d_lut);
   (void)hipFree(d.d_lut_k);
   (void)hipFree(d.d_lut8);
+  (void)hipFree(d.d_lut13);
   for (auto& Ld : d.lists) {
     (void)hipFree(Ld.mod);
     (void)hipFree(Ld.tail);
@@ -118,12 +120,14 @@ int init_device(DeviceState& d, const HostTables* T) {
   HIP_TRY(hipMalloc(&d.d_lut, T->lut.size() * sizeof(uint16_t)));
   HIP_TRY(hipMalloc(&d.d_lut_k, T->lut_k.size() * sizeof(uint32_t)));
   HIP_TRY(hipMalloc(&d.d_lut8, sizeof(T->lut8)));
+  HIP_TRY(hipMalloc(&d.d_lut13, sizeof(T->lut13)));
   HIP_TRY(hipMemcpy(d.d_mod, &T->mod, sizeof(ModConst), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(d.d_crt, T->crt, sizeof(CrtConst) * (kMaxModuli + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(d.d_lut, T->lut.data(), T->lut.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(d.d_lut_k, T->lut_k.data(), T->lut_k.size() * sizeof(uint32_t),
                     hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(d.d_lut8, T->lut8, sizeof(T->lut8), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(d.d_lut13, T->lut13, sizeof(T->lut13), hipMemcpyHostToDevice));
   for (int h = 1; h <= kMaxHeads; ++h) {
     const HostTables::List& Lh = T->lists[h];
     DeviceState::List& Ld = d.lists[h];
@@ -642,7 +646,7 @@ int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double
   if (last < 1) return OZFP4_OK;
 
   HIP_TRY(encode_stages(d, a, b, [&](const ConvOperand& x, const ConvOperand& y) {
-    return launch_encode_ozi(g_stream, x, y, p.nplanes);
+    return launch_encode_ozi(g_stream, x, y, p.nplanes, d->d_lut13);
   }));
   record(d, 3);
   if (last < 3) return OZFP4_OK;

@@ -249,6 +249,12 @@ struct CrtConst {
   uint64_t P[3];             // P as a 192-bit integer
 };
 
+// Scheme-I encoder table: entry r + kLut13Half for a remainder r modulo 2197,
+// |r| <= kLut13Half: codes of its three greedy limbs in bytes 0 to 2, and in
+// byte 3 one more than the carry (r - (c0 + 13 c1 + 169 c2)) / 2197.
+constexpr int kLut13Half = 1104;
+constexpr int kLut13Entries = 2 * kLut13Half + 1;
+
 struct HostTables {
   std::vector<int> moduli;                 // 20, greedy order
   ModConst mod;
@@ -257,6 +263,7 @@ struct HostTables {
   std::vector<uint32_t> lut_k;             // encoder LUT of the Karatsuba mode
   int nk[kMaxModuli + 1];                  // Karatsuba moduli among the first L
   uint16_t lut8[256];                      // int8 -> three limb codes
+  uint32_t lut13[kLut13Entries];           // scheme I: r -> three limb codes and carry
   Big P[kMaxModuli + 1];                   // product of the first L moduli
   // the lists with h = 1..kMaxHeads one-limb heads (index h; 0 unused)
   struct List {
@@ -378,6 +385,19 @@ inline bool build_tables(HostTables& T) {
     }
     if (rest != 0) return false;
     T.lut8[v + 128] = (uint16_t)codes;
+  }
+  for (int r = -kLut13Half; r <= kLut13Half; ++r) {
+    int rest = r;
+    uint32_t codes = 0;
+    for (int i = 0; i < 3; ++i) {
+      const int c = greedy13(rest);
+      const int code = e2m1_code_of_limb(c);
+      if (code < 0) return false;
+      codes |= (uint32_t)code << (8 * i);
+      rest = (rest - c) / 13;
+    }
+    if (rest < -1 || rest > 1) return false;
+    T.lut13[r + kLut13Half] = codes | (uint32_t)(rest + 1) << 24;
   }
   if (!build_crt(T.moduli, T.crt, T.P)) return false;
 
