@@ -42,6 +42,11 @@ CASES = [
     (1030, 900, 700, 18, "random"),
 ]
 
+# outputs of enough tiles that a block runs several moduli (k up to 512):
+# whole and short last groups, 1 to 8 stages a modulus
+GROUPED = [(2600, 2500, 30, 18), (2560, 2700, 64, 19), (3000, 2300, 130, 23), (2500, 2600, 257, 18),
+           (2300, 3100, 512, 18), (5000, 4900, 200, 18)]
+
 
 def _inputs(m, n, k, kind):
     if kind == "random":
@@ -68,6 +73,23 @@ def test_residues_of_short_products(gpu_lib, m, n, k, L, kind):
         rb = o.residues(Bi, q).astype(np.float64)
         want = np.mod(np.rint(ra @ rb).astype(np.int64), q)
         assert np.array_equal(R[l].T.astype(np.int64), want), f"modulus {q}"
+
+
+@pytest.mark.parametrize("m,n,k,L", GROUPED)
+def test_residues_of_several_moduli_a_block(gpu_lib, m, n, k, L):
+    import torch
+    A, B = dgemm_inputs(m, n, k, 0.5, SEED + m + k)
+    moduli = o.select_moduli(L)
+    cA, cB = o.capacity_bits(k, moduli)
+    Ai = o.to_integers(A, o.shift_exponents(A, axis=1, c=cA), axis=1)
+    Bi = o.to_integers(B, o.shift_exponents(B, axis=0, c=cB), axis=0)
+    announce(f"several moduli a block m={m} n={n} k={k} L={L}")
+    R = gpu_lib.residues(dev_cm(A), dev_cm(B), L)
+    for l, q in enumerate(moduli):   # the vendor's FP64 product is exact here
+        ra = torch.from_numpy(o.residues(Ai, q).astype(np.float64)).cuda()
+        rb = torch.from_numpy(o.residues(Bi, q).astype(np.float64)).cuda()
+        want = torch.remainder(torch.round(ra @ rb).to(torch.int64), q).to(torch.uint8)
+        assert torch.equal(R[l].t(), want), f"modulus {q}"
 
 
 def test_split_route_in_k_ranges(gpu_lib):
