@@ -274,8 +274,20 @@ def colmajor(X):
     return X.t().contiguous().t()
 
 
+_torch = None
+
+
+def _th():
+    """torch, imported on the first use of a torch helper."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _check_operand(X, dtype, name):
-    import torch
+    torch = _th()
     if not isinstance(X, torch.Tensor) or X.dim() != 2:
         raise TypeError(f"{name} must be a 2-D torch tensor")
     if X.dtype != dtype:
@@ -316,9 +328,17 @@ def _product(op, A, B, in_dtype, out_dtype, count, out, where):
     if C.shape != (m, n) or C.dtype != out_dtype or (C.stride(0) != 1 and m > 1):
         raise ValueError(f"out must be a column-major {str(out_dtype).split('.')[-1]} (m x n) tensor")
     ldc = max(1, C.stride(1) if n > 1 else m)
-    with _on(A.device, B, C):
-        _check(ozfp4_product(op, m, n, k, A.data_ptr(), a_rs, a_cs, B.data_ptr(), b_rs, b_cs,
-                             C.data_ptr(), ldc, count), where)
+    args = (op, m, n, k, A.data_ptr(), a_rs, a_cs, B.data_ptr(), b_rs, b_cs, C.data_ptr(), ldc, count)
+    torch, dev = _th(), A.get_device()
+    if B.get_device() == dev == C.get_device() == torch.cuda.current_device():
+        # as _on, whose context manager costs a small call 3 us
+        lib = load()
+        lib.ozfp4_set_stream(torch.cuda.current_stream(dev).cuda_stream)
+        code = lib.ozfp4_product(*args)
+    else:
+        with _on(A.device, B, C):
+            code = ozfp4_product(*args)
+    _check(code, where)
     return C
 
 
@@ -337,14 +357,13 @@ def _on(device, *tensors):
 
 
 def _empty_cm(rows, cols, dtype, device):
-    import torch
-    return torch.empty_strided((rows, cols), (1, max(1, rows)), dtype=dtype, device=device)
+    return _th().empty_strided((rows, cols), (1, max(1, rows)), dtype=dtype, device=device)
 
 
 def dgemm(A, B, n_moduli: int = 19, out=None):
     """C = fl(A B) for float64 device tensors A (m x k), B (k x n) by Ozaki
     scheme II on FP4 limbs; returns C (m x n), column-major."""
-    import torch
+    torch = _th()
     return _product(OZFP4_OP_DGEMM, A, B, torch.float64, torch.float64, n_moduli, out, "ozfp4_dgemm")
 
 
@@ -352,7 +371,7 @@ def dgemm_split(A, B, n_moduli: int = 19, out=None):
     """C = fl(A B) for float64 device tensors by scheme II with the two-term
     split of the converted operands (ozfp4_dgemm_split); returns C (m x n),
     column-major."""
-    import torch
+    torch = _th()
     return _product(OZFP4_OP_DGEMM_SPLIT, A, B, torch.float64, torch.float64, n_moduli, out,
                     "ozfp4_dgemm_split")
 
@@ -361,7 +380,7 @@ def dgemm_noalloc(A, B, out, n_moduli: int = 19):
     """ozfp4_dgemm_noalloc into the caller's column-major float64 tensor
     `out` (m x n): the library allocates nothing; the current device must
     have been set up (ozfp4_init)."""
-    import torch
+    torch = _th()
     if not isinstance(out, torch.Tensor):
         raise ValueError("out must be a column-major float64 (m x n) tensor")
     return _product(OZFP4_OP_DGEMM_NOALLOC, A, B, torch.float64, torch.float64, n_moduli, out,
@@ -371,7 +390,7 @@ def dgemm_noalloc(A, B, out, n_moduli: int = 19):
 def igemm_s8(A, B, out=None):
     """C = A B for int8 device tensors, int32 result wrapping modulo 2^32;
     returns C (m x n), column-major."""
-    import torch
+    torch = _th()
     return _product(OZFP4_OP_IGEMM_S8, A, B, torch.int8, torch.int32, 0, out, "ozfp4_igemm_s8")
 
 
@@ -429,7 +448,7 @@ def dgemm_ozi(A, B, n_limbs: int = OZFP4_OZI_MAX_LIMBS, out=None):
     """C = fl(A B) for float64 device tensors A (m x k), B (k x n) by Ozaki
     scheme I on FP4 limbs with n_limbs limbs per operand; returns C (m x n),
     column-major."""
-    import torch
+    torch = _th()
     return _product(OZFP4_OP_DGEMM_OZI, A, B, torch.float64, torch.float64, n_limbs, out,
                     "ozfp4_dgemm_ozi")
 
@@ -485,7 +504,7 @@ def sgemm(A, B, n_moduli: int | None = None, out=None):
     """C = fl32(A B) for float32 device tensors A (m x k), B (k x n) by Ozaki
     scheme II on FP4 limbs; n_moduli defaults to the fewest moduli with
     24-bit capacities for this k. Returns C (m x n), column-major."""
-    import torch
+    torch = _th()
     # 0 is the library's own choice (that of sgemm_moduli); a caller's 0 stays
     # the error that any count below 2 is
     count = 0 if n_moduli is None else (n_moduli or 1)
