@@ -12,20 +12,22 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libozfp4.so")
-# ten translation units: the API with the default kernels, the conversion
+# eleven translation units: the API with the default kernels, the conversion
 # stage (line maxima, encoder), the Karatsuba mode's kernels, the scheme-I
 # kernels, the FP32-emulation kernels, the two-term split's kernels, the
 # one-limb modulus's GEMM, the residue GEMM for short products, the INT8
-# encoder and short GEMM, and the reference-measurement kernels (kept apart so
-# they cannot change the default kernels' code)
+# encoder and short GEMM, scheme I's short GEMM, and the reference-measurement
+# kernels (kept apart so they cannot change the default kernels' code)
 SOURCES = [os.path.join(HERE, "csrc", n)
            for n in ("ozfp4.hip", "convert.hip", "karatsuba.hip", "ozaki1.hip", "sgemm.hip",
-                     "split.hip", "onelimb.hip", "gemm_short.hip", "igemm.hip", "calibrate.hip")]
+                     "split.hip", "onelimb.hip", "gemm_short.hip", "igemm.hip", "ozaki1_short.hip",
+                     "calibrate.hip")]
 HEADERS = [os.path.join(HERE, "csrc", n) for n in
            ("device_common.hpp", "kernels.hpp", "karatsuba.hpp", "crt_round.hpp", "tables.hpp",
             "ozaki1.hpp", "ozi_round.hpp", "sgemm.hpp", "crt_round_f32.hpp",
             "calibrate.hpp", "split.hpp", "crt_split.hpp", "onelimb.hpp", "gemm_short.hpp", "igemm.hpp",
-            "convert.hpp", "encode.hpp", "plain_gemm.hpp", "limb3_sched.hpp")] + \
+            "convert.hpp", "encode.hpp", "plain_gemm.hpp", "limb3_sched.hpp",
+            "limb3_short.hpp")] + \
           [os.path.join(ROOT, "include", "ozfp4.h")]
 
 # -packed-fp32-ops: keep the compiler from emitting packed FP32 arithmetic.

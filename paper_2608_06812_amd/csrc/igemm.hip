@@ -5,6 +5,7 @@
 
 #include "device_common.hpp"
 #include "igemm.hpp"
+#include "limb3_short.hpp"
 
 namespace ozfp4 {
 
@@ -132,43 +133,26 @@ __global__ __launch_bounds__(256) void k_encode_s8(S8Operand a, S8Operand b, uin
 }
 
 // ------------------------------------------------------------ short GEMM
-// Block tile 128 x 64, four waves (one per SIMD) of 64 x 32 with the INT8
-// GEMM's five accumulator sets, k in stages of one 64-wide fragment: 18
-// fragments (A: 3 planes x 4 line blocks, then B: 3 planes x 2), 18 KiB, in
-// a 4-slot LDS ring of 72 KiB. Two such blocks fit a CU, and one's first
-// copies, epilogue and stores run under the other's MFMAs; the 128 x 128
-// block of the long GEMM has its CU to itself. The price is half as many
-// operand bytes per MFMA again (256 against 171).
-constexpr int kS8sWaves = 4;
-constexpr int kS8sRing = 4;
-constexpr int kS8sFrags = 18;
-constexpr int kS8sStage = kS8sFrags * kFragBytes;
-constexpr int kS8sDma = 5;   // copies of waves 0 and 1 a stage; waves 2 and 3 issue 4
-
-__device__ __forceinline__ constexpr int fragA8s(int p, int rb) { return (p * 4 + rb) * kFragBytes; }
-__device__ __forceinline__ constexpr int fragB8s(int p, int cb) { return (12 + p * 2 + cb) * kFragBytes; }
-
-__global__ __launch_bounds__(kS8sWaves * 64, 2) void k_gemm_s8_short(ShortS8 g, int nst_all,
+// The main loop of limb3_short.hpp over one k range of one 128 x 64 tile.
+__global__ __launch_bounds__(kL3Waves * 64, 2) void k_gemm_s8_short(ShortS8 g, int nst_all,
                                                                      int64_t tiles_m,
                                                                      int64_t tiles_n,
                                                                      int64_t nblocks) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[kS8sRing * kS8sStage];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kL3Ring * kL3Stage];
   int part;
   int64_t tm, tn;
   tile_coords(blockIdx.x, nblocks, tiles_m, tiles_n, &part, &tm, &tn, 72);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int rbw = 2 * wm;   // this wave's first A line block; its B line block is wn
   const int st0 = (int)((int64_t)nst_all * part / g.nsplit);
   const int nst = (int)((int64_t)nst_all * (part + 1) / g.nsplit) - st0;
-  const bool five = wave < 2;
 
   // fragment f = wave + 4 j of a stage (waves 2 and 3: j < 4)
-  __amdgpu_buffer_rsrc_t src[kS8sDma];
+  __amdgpu_buffer_rsrc_t src[kL3Dma];
 #pragma unroll
-  for (int j = 0; j < kS8sDma; ++j) {
-    const int f = min(wave + 4 * j, kS8sFrags - 1);
+  for (int j = 0; j < kL3Dma; ++j) {
+    const int f = min(wave + 4 * j, kL3Frags - 1);
     const uint8_t* base;
     if (f < 12)
       base = g.pa + (int64_t)(f >> 2) * g.plane_a + ((tm * 4 + (f & 3)) * g.kblocks + st0) * kFragBytes;
@@ -177,26 +161,11 @@ __global__ __launch_bounds__(kS8sWaves * 64, 2) void k_gemm_s8_short(ShortS8 g, 
     src[j] = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nst * kFragBytes, kBufferWord3);
   }
   const int lane16 = lane * 16;
-  auto dma = [&](int st, int j) {
-    dma16_buf(src[j], (uint32_t)lane16, (uint32_t)(st * kFragBytes),
-              lds + (st % kS8sRing) * kS8sStage + (wave + 4 * j) * kFragBytes);
+  int copied = 0;   // next stage to copy
+  auto copy = [&](int j) {
+    dma16_buf(src[j], (uint32_t)lane16, (uint32_t)(copied * kFragBytes),
+              lds + (copied % kL3Ring) * kL3Stage + (wave + 4 * j) * kFragBytes);
   };
-  auto dma_last = [&](int st) {
-    if (five) dma(st, 4);
-  };
-  // at most `stages` (0..3) newer stages' copies of this wave in flight
-  auto wait = [&](int stages) {
-    if (stages >= 3) {
-      if (five) wait_vm_lgkm0<15>(); else wait_vm_lgkm0<12>();
-    } else if (stages == 2) {
-      if (five) wait_vm_lgkm0<10>(); else wait_vm_lgkm0<8>();
-    } else if (stages == 1) {
-      if (five) wait_vm_lgkm0<5>(); else wait_vm_lgkm0<4>();
-    } else {
-      wait_vm_lgkm0<0>();
-    }
-  };
-
   v16f acc[5][2];
 #pragma unroll
   for (int e = 0; e < 5; ++e)
@@ -204,73 +173,15 @@ __global__ __launch_bounds__(kS8sWaves * 64, 2) void k_gemm_s8_short(ShortS8 g, 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[e][i][v] = 0.0f;
-  v4i a[3][2], b[3];
-  auto group = [&](int p, int q) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) acc[p + q][i] = mfma_fp4(a[p][i], b[q], acc[p + q][i]);
-  };
-  auto readA = [&](const uint8_t* sb, int p) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[p][i] = *reinterpret_cast<const v4i*>(sb + fragA8s(p, rbw + i) + lane16);
-  };
-  auto readB = [&](const uint8_t* sb, int p) {
-    b[p] = *reinterpret_cast<const v4i*>(sb + fragB8s(p, wn) + lane16);
-  };
-  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
-
-  // Stage s multiplies the operands in registers, and as a register's last
-  // group has been issued refills it for stage s + 1 (every read has at least
-  // two groups, four MFMAs of the wave, to land in). The handover after the
-  // first group makes stage s + 1 visible and frees the slot of stage s,
-  // which takes stage s + 4. `after`: stages after s.
-  auto stage = [&](int s, int after) {
-    const uint8_t* nb = lds + ((s + 1) % kS8sRing) * kS8sStage;
-    const bool next = after > 0, copy = after >= kS8sRing;
-    auto cp = [&](int j) {
-      if (copy) dma(s + kS8sRing, j);
-    };
-    group(0, 0); fence();
-    if (next) {
-      wait(min(after - 1, 2));
-      block_sync();
-    }
-    group(0, 1); cp(0); fence();
-    group(0, 2); fence(); if (next) readA(nb, 0); fence();
-    group(1, 0); cp(1); fence();
-    group(2, 0); fence(); if (next) readB(nb, 0); fence();
-    group(1, 1); cp(2); fence();
-    group(1, 2); fence(); if (next) readA(nb, 1); fence();
-    group(2, 1); cp(3); fence(); if (next) readB(nb, 1); fence();
-    group(2, 2); if (copy) dma_last(s + kS8sRing); fence();
-    if (next) { readA(nb, 2); readB(nb, 2); }
-    fence();
-  };
-
-  const int first = min(nst, kS8sRing);
-  for (int st = 0; st < first; ++st) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma(st, j);
-    dma_last(st);
-  }
-  wait(first - 1);
-  block_sync();
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    readA(lds, p);
-    readB(lds, p);
-  }
-  fence();
-  int s = 0;
-  for (; s + kS8sRing < nst; ++s) stage(s, kS8sRing);
-  for (; s < nst; ++s) stage(s, nst - 1 - s);
+  limb3_short_run(lds, nst, wave, lane16, copy, [&] { ++copied; }, acc);
 
   // sum_g 13^g 4 acc_g: |4 acc_g| <= 192 k < 2^23 for k <= 40960, so the
   // 24-bit multiplies are exact; the sum wraps modulo 2^32
   const bool direct = g.nsplit == 1;
   int32_t* C = direct ? g.C : g.partial + (int64_t)part * g.m_pad * g.n_pad;
   const int64_t ldc = direct ? g.ldc : g.m_pad, m = direct ? g.m : g.m_pad, n = direct ? g.n : g.n_pad;
-  const int64_t col = tn * kS8ShortN + wn * 32 + (lane & 31);
-  const int64_t row0 = tm * kS8ShortM + wm * 64 + (lane >> 5) * 4;
+  const int64_t col = tn * kL3TileN + wn * 32 + (lane & 31);
+  const int64_t row0 = tm * kL3TileM + wm * 64 + (lane >> 5) * 4;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -339,7 +250,7 @@ hipError_t launch_encode_s8(hipStream_t stream, const S8Operand& a, const S8Oper
 }
 
 int short_s8_split(int64_t m, int64_t n, int64_t k) {
-  const int64_t blocks = ((m + kS8ShortM - 1) / kS8ShortM) * ((n + kS8ShortN - 1) / kS8ShortN);
+  const int64_t blocks = ((m + kL3TileM - 1) / kL3TileM) * ((n + kL3TileN - 1) / kL3TileN);
   const int nst = stages_of(k), least = (int)((k + kS8ShortRange - 1) / kS8ShortRange);
   if (least > 16) return least;   // the caller's rule sends these to the long GEMM
   int best = least;
@@ -350,10 +261,10 @@ int short_s8_split(int64_t m, int64_t n, int64_t k) {
 }
 
 hipError_t launch_gemm_s8_short(hipStream_t stream, const ShortS8& g) {
-  const int64_t tiles_m = (g.m + kS8ShortM - 1) / kS8ShortM;
-  const int64_t tiles_n = (g.n + kS8ShortN - 1) / kS8ShortN;
+  const int64_t tiles_m = (g.m + kL3TileM - 1) / kL3TileM;
+  const int64_t tiles_n = (g.n + kL3TileN - 1) / kL3TileN;
   const int64_t nblocks = tiles_m * tiles_n * g.nsplit;
-  hipLaunchKernelGGL(k_gemm_s8_short, dim3((unsigned)nblocks), dim3(kS8sWaves * 64), 0, stream, g,
+  hipLaunchKernelGGL(k_gemm_s8_short, dim3((unsigned)nblocks), dim3(kL3Waves * 64), 0, stream, g,
                      stages_of(g.k), tiles_m, tiles_n, nblocks);
   if (g.nsplit > 1) {
     const uint32_t threads = (uint32_t)(g.m * g.n);

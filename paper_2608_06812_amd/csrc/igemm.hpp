@@ -23,7 +23,6 @@ struct S8Operand {
 hipError_t launch_encode_s8(hipStream_t stream, const S8Operand& a, const S8Operand& b,
                             const uint16_t* lut8);
 
-constexpr int kS8ShortM = 128, kS8ShortN = 64;   // block tile of the short GEMM
 constexpr int64_t kS8ShortRange = 40960;         // longest k range of a block
 
 // C = A B (m x n, wrapping int32) from the limb planes, k cut into nsplit

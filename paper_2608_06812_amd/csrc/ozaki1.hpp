@@ -19,6 +19,14 @@ hipError_t launch_gemm_ozi(hipStream_t stream, const uint8_t* PA, const uint8_t*
                            int64_t plane_a, int64_t plane_b, int64_t kblocks, int64_t m_pad,
                            int64_t n_pad, int nblk);
 
+// the same over the 128 x 64 tiles that meet the m x n output, for k at most
+// kOziShortK (ozaki1_short.hip)
+constexpr int64_t kOziShortK = 8192;
+hipError_t launch_gemm_ozi_short(hipStream_t stream, const uint8_t* PA, const uint8_t* PB,
+                                 int64_t* H, int64_t plane_a, int64_t plane_b, int64_t kblocks,
+                                 int64_t m, int64_t n, int64_t k, int64_t m_pad, int64_t n_pad,
+                                 int nblk);
+
 // k_ozi_reduce: C = RN(sum_h 2197^h H_h 2^-(s_i + t_j))
 hipError_t launch_ozi_reduce(hipStream_t stream, const int64_t* H, int64_t ldh, int64_t hplane,
                              int nh, int64_t m, int64_t n, const uint64_t* amaxA,

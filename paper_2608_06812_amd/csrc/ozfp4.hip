@@ -628,6 +628,16 @@ void make_ozi_plan(int64_t m, int64_t n, int64_t k, int p, OziPlan* o) {
   o->total = off;
 }
 
+// Which scheme-I GEMM: 128 x 128 units, one a CU, or 128 x 64 units, two a CU
+// (ozaki1_short.hip). GEMM, us, in that order, 15 limbs: 25.6 / 9.5 at 64^3,
+// 108 / 102 at 1024^3, 224 / 211 at 2048 x 2048 x 512, 1465 / 1480 at 4096 x
+// 4096 x 1024, 690 / 697 at 2048^3: short k, or under four units a CU (325 /
+// 202 at 100 x 90 x 8000).
+bool use_short_ozi(int64_t m, int64_t n, int64_t k, int nh) {
+  const int64_t units = ((m + 127) / 128) * ((n + 127) / 128) * nh;
+  return k <= 768 || (k <= kOziShortK && units < 1024);
+}
+
 // Stages, stopping after `last`: 0 scale, 1 encode A, 2 encode B, 3 limb
 // GEMM into the partial-sum planes, 4 reduction into C.
 int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
@@ -637,8 +647,9 @@ int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double
   uint8_t* pb = planes_b_out ? planes_b_out : ws + p.off_pb;
   int64_t* H = reinterpret_cast<int64_t*>(ws + p.off_h);
   ConvOperand a, b;
+  const bool use_short = use_short_ozi(p.m, p.n, p.k, p.nh);
   conv_operands(p, A, B, p.cap, p.cap, ws, pa, pb, p.off_h, &a, &b,
-                planes_a_out ? 0 : p.kblocks);
+                planes_a_out ? 0 : frags_read(use_short, p.k, p.kblocks));
 
   record(d, 0);
   HIP_TRY(launch_line_max(g_stream, false, a, b, flag));
@@ -651,8 +662,12 @@ int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double
   record(d, 3);
   if (last < 3) return OZFP4_OK;
 
-  HIP_TRY(launch_gemm_ozi(g_stream, pa, pb, H, p.plane_a, p.plane_b, p.kblocks, p.m_pad, p.n_pad,
-                          p.nblk));
+  if (use_short)
+    HIP_TRY(launch_gemm_ozi_short(g_stream, pa, pb, H, p.plane_a, p.plane_b, p.kblocks, p.m, p.n, p.k,
+                                  p.m_pad, p.n_pad, p.nblk));
+  else
+    HIP_TRY(launch_gemm_ozi(g_stream, pa, pb, H, p.plane_a, p.plane_b, p.kblocks, p.m_pad, p.n_pad,
+                            p.nblk));
   record(d, 4);
   if (last < 4) return OZFP4_OK;
 
