@@ -521,7 +521,9 @@ int ozfp4_profile(int enable);
  * count to the HOST *n_stages (0 if no profiled call ran). Returns OZFP4_OK,
  * or OZFP4_EINVAL for a null pointer or max < 0. dgemm and sgemm stages:
  * 0 scale, 1 encode A, 2 encode B, 3 residue GEMM, 4 CRT (dgemm_split: the
- * same, each encode covering both terms, the GEMM stage all four products). dgemm_ozi stages:
+ * same, each encode covering both terms, the GEMM stage all four products);
+ * a profiled call encodes A and B in a launch each, any other call in one.
+ * dgemm_ozi stages:
  * 0 scale, 1 encode A, 2 encode B, 3 limb GEMM, 4 reduction. igemm_s8
  * stages: 0 encode A, 1 encode B, 2 GEMM (asynchronous: this call waits for
  * its last event, and so does the next call of the library that records
