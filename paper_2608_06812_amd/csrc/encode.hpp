@@ -5,6 +5,7 @@
 
 #include "convert.hpp"
 #include "device_common.hpp"
+#include "encode_address.hpp"
 
 namespace ozfp4 {
 
@@ -60,7 +61,7 @@ __device__ __forceinline__ uint32_t entry_address(double x, uint16_t xl, double 
     xl = (uint16_t)(e * (uint32_t)__double_as_longlong(x + 0x1.8p52));
   }
   const uint16_t q = (uint16_t)__double_as_longlong(__builtin_fma(x, inv, magic));
-  return (uint16_t)(q * step + xl);
+  return entry_sum(q, step, xl);
 }
 
 template <bool kKar, bool kWide, typename TIn, int kTerms>
@@ -152,10 +153,9 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
       // LDS address of the table entry of remainder 0, and the offset q0 of
       // the quotients with q0 E m = -address modulo 2^16
       const uint32_t zero = lds_base + kE * (uint32_t)(mc->lut_off[l] - word0 * kPerWord + m);
-      const uint32_t q0 =
-          ((uint32_t)(-(int)(zero / kE)) >> mc->twos[l]) * (uint32_t)mc->odd_inv[l] & (0xffffu / kE);
+      const uint32_t q0 = entry_quotient_offset(zero, kE, mc->twos[l], mc->odd_inv[l]);
       const double magic = 0x1.8p52 + (double)q0;
-      const uint16_t step = (uint16_t)(0u - kE * (uint32_t)m);
+      const uint16_t step = entry_step(kE, m);
       uint32_t w0[4], w1[4], w2[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
