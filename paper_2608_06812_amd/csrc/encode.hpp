@@ -26,8 +26,9 @@ namespace ozfp4 {
 //   bits then hold q + q0, and one 16-bit multiply-add gives
 //   E x - (q + q0) E m with E x modulo 2^16 kept from the conversion; q0 is
 //   chosen so that -q0 E m is the address `zero` of remainder 0. (An even
-//   m = odd 2^z needs zero / E divisible by 2^z: tables start at multiples of
-//   16 entries, and m <= 169 has z <= 4.)
+//   m = odd 2^z needs zero / E divisible by 2^z: the tables' array is aligned
+//   to 16 entries, tables start at multiples of 16 entries within it, and
+//   m <= 169 has z <= 4.)
 //   Two VALU operations a value and modulus before the lookup, in place of
 //   four in FP64: both operands at 2048^3 67 -> 61 us (18 moduli), 1500 x 3001
 //   44.6 -> 38.2 us, FP32 2048^3 48 -> 43 us. Large operands are bound by
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
     const ModConst* __restrict__ mc, const void* __restrict__ lut, int d2) {
   typedef typename std::conditional<kKar, uint32_t, uint16_t>::type Entry;
   constexpr uint32_t kE = (uint32_t)sizeof(Entry);
-  extern __shared__ __attribute__((aligned(16))) uint8_t s_raw[];
+  extern __shared__ __attribute__((aligned(kLutAlign))) uint8_t s_raw[];
   const bool is_b = blockIdx.x >= blocks_a;
   const uint32_t block = is_b ? blockIdx.x - blocks_a : blockIdx.x;
   const uint32_t nblocks = is_b ? gridDim.x - blocks_a : blocks_a;

@@ -9,6 +9,11 @@
 
 namespace ozfp4 {
 
+// Alignment of the tables in LDS. A table starts at a multiple of 16 entries
+// from the array's base, so the base has to be a multiple of 16 entries too
+// for every m = odd 2^z, z <= 4, and entries of up to four bytes.
+constexpr uint32_t kLutAlign = 64;
+
 // q0 with -q0 e m = zero modulo 2^16, for tables of e-byte entries and
 // m = odd 2^twos: zero, the address of the entry of remainder 0, has to be
 // divisible by e 2^twos.

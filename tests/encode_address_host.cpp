@@ -1,6 +1,7 @@
 // Host build of the encoder's table addresses (encode_address.hpp), for
 // tests/test_encode_address_host.py: every quotient and remainder of every
-// modulus of every list, both entry sizes, a group starting at any modulus.
+// modulus of every list, both entry sizes, a group starting at any modulus,
+// the tables' array at any base that its alignment allows.
 // Prints the number of addresses checked; exit code 1 at a wrong one.
 #include <cstdio>
 
@@ -41,9 +42,11 @@ static bool check_list(const ModConst& mc, int L, uint32_t e, uint32_t base) {
 int main() {
   static HostTables T;
   if (!build_tables(T)) return 2;
-  if (!check_list(T.mod, kMaxModuli, 2, 0) || !check_list(T.mod, kMaxModuli, 4, 0)) return 1;
-  for (int h = 1; h <= kMaxHeads; ++h)
-    if (!check_list(T.lists[h].mod, kMaxModuli, 2, 0)) return 1;
+  for (uint32_t base : {0u, kLutAlign, 3 * kLutAlign, 16 * kLutAlign}) {
+    if (!check_list(T.mod, kMaxModuli, 2, base) || !check_list(T.mod, kMaxModuli, 4, base)) return 1;
+    for (int h = 1; h <= kMaxHeads; ++h)
+      if (!check_list(T.lists[h].mod, kMaxModuli, 2, base)) return 1;
+  }
   std::printf("%lld\n", g_checked);
   return 0;
 }

@@ -30,4 +30,4 @@ def run(tmp_path_factory):
 
 def test_every_address_is_its_entry(run):
     assert run.returncode == 0, run.stdout + run.stderr
-    assert int(run.stdout) > 27 * 65536 * 7      # every quotient of every modulus and list
+    assert int(run.stdout) > 4 * 27 * 65536 * 7      # every quotient of every modulus and list
