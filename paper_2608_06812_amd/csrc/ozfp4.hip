@@ -54,7 +54,8 @@ struct DeviceState {
   uint8_t* ws = nullptr;
   size_t ws_bytes = 0;
   int* h_flag = nullptr;      // pinned host word for the non-finite flag,
-  int* h_flag_dev = nullptr;  // and its device address
+  int* h_flag_dev = nullptr;  // its device address,
+  bool flag_open = false;     // and whether a call's kernels may still write it
   hipEvent_t ev[kMaxStages + 1] = {};
   uint8_t* scratch = nullptr; // this device's address of the scratch array
   int cus_per_xcd = 1;        // CUs of one of the 8 XCDs
@@ -345,8 +346,12 @@ void record(DeviceState* d, int i) {
 // The flag word of a call about to start, zero: the line-maximum kernel
 // writes host memory directly where a value is NaN or infinite, so the call
 // ends with its last kernel and not with a copy of the flag (a 3.4 us copy
-// kernel and its gap).
+// kernel and its gap). The host's zero is not ordered with the stream, so a
+// call that ended early (a launch failed), with its line maxima perhaps still
+// to run, is waited for first. Null if that wait fails.
 int* start_flag(DeviceState* d) {
+  if (d->flag_open && hipDeviceSynchronize() != hipSuccess) return nullptr;
+  d->flag_open = true;
   *static_cast<volatile int*>(d->h_flag) = 0;
   return d->h_flag_dev;
 }
@@ -487,8 +492,10 @@ int ensure_plan(DeviceState* d, Plan* p) {
 // Stages of the dgemm pipeline, stopping after `last`:
 // 0 scale, 1 encode A, 2 encode B, 3 residue GEMM, 4 CRT.
 // A, B and C are double, or float when p.f32.
-int run_dgemm(const DgemmPlan& p, DeviceState* d, const Mat& A, const Mat& B, void* Cv, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
-              uint8_t* planes_b_out, uint8_t* ws_base = nullptr) {
+int run_dgemm(const DgemmPlan& p, DeviceState* d, const Mat& A, const Mat& B, void* Cv,
+              int64_t ldc, int last, int* flag, uint8_t* planes_a_out, uint8_t* planes_b_out,
+              uint8_t* ws_base = nullptr) {
+  if (!flag) return OZFP4_EHIP;
   const HostTables* T = tables();
   uint8_t* ws = ws_base ? ws_base : d->ws;
   unsigned* arrive = reinterpret_cast<unsigned*>(ws + p.off_flag) + 32;
@@ -640,8 +647,9 @@ bool use_short_ozi(int64_t m, int64_t n, int64_t k, int nh) {
 
 // Stages, stopping after `last`: 0 scale, 1 encode A, 2 encode B, 3 limb
 // GEMM into the partial-sum planes, 4 reduction into C.
-int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C, int64_t ldc, int last, int* flag, uint8_t* planes_a_out,
-            uint8_t* planes_b_out) {
+int run_ozi(const OziPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C, int64_t ldc,
+            int last, int* flag, uint8_t* planes_a_out, uint8_t* planes_b_out) {
+  if (!flag) return OZFP4_EHIP;
   uint8_t* ws = d->ws;
   uint8_t* pa = planes_a_out ? planes_a_out : ws + p.off_pa;
   uint8_t* pb = planes_b_out ? planes_b_out : ws + p.off_pb;
@@ -688,6 +696,7 @@ int prepare_ozi(int64_t m, int64_t n, int64_t k, int n_limbs, OziPlan* p, Device
 // an input is not finite.
 int finish_with_flag(DeviceState* d, int nstages) {
   HIP_TRY(hipStreamSynchronize(g_stream));
+  d->flag_open = false;
   if (g_profile && nstages > 0) {
     g_pending_stages = 0;
     for (int i = 0; i < nstages; ++i) {
@@ -746,7 +755,9 @@ int make_split_plan(int64_t m, int64_t n, int64_t k, int L, SplitPlan* p) {
 
 // Stages: 0 scale, 1 encode A (both terms), 2 encode B (both terms), 3 the
 // four residue GEMMs, 4 the combined CRT.
-int run_split(const SplitPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C, int64_t ldc, int* flag) {
+int run_split(const SplitPlan& p, DeviceState* d, const Mat& A, const Mat& B, double* C,
+              int64_t ldc, int* flag) {
+  if (!flag) return OZFP4_EHIP;
   const HostTables* T = tables();
   uint8_t* ws = d->ws;
   unsigned* arrive = reinterpret_cast<unsigned*>(ws + p.off_flag) + 32;
