@@ -26,7 +26,7 @@ HEADERS = [os.path.join(HERE, "csrc", n) for n in
            ("device_common.hpp", "kernels.hpp", "karatsuba.hpp", "crt_round.hpp", "tables.hpp",
             "ozaki1.hpp", "ozi_round.hpp", "sgemm.hpp", "crt_round_f32.hpp",
             "calibrate.hpp", "split.hpp", "crt_split.hpp", "onelimb.hpp", "gemm_short.hpp", "igemm.hpp",
-            "convert.hpp", "encode.hpp", "encode_address.hpp", "plain_gemm.hpp", "limb3_sched.hpp",
+            "convert.hpp", "encode.hpp", "encode_address.hpp", "plain_gemm.hpp", "limb3_sched.hpp", "routes.hpp",
             "limb3_short.hpp")] + \
           [os.path.join(ROOT, "include", "ozfp4.h")]
 

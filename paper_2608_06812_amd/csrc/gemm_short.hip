@@ -1,10 +1,9 @@
 // The residue GEMM for short products: few stages or few tiles. A
 // translation unit of its own, so nothing here can change how the compiler
 // schedules the default kernels.
-#include <algorithm>
-
 #include "device_common.hpp"
 #include "gemm_short.hpp"
+#include "routes.hpp"
 
 namespace ozfp4 {
 
@@ -19,6 +18,7 @@ namespace {
 // kernel has its CU to itself, so a block pays those in full: about 7 us,
 // against 0.43 us of MFMA time per k = 64. The price is a third more operand
 // bytes per MFMA (256 against 192), which is why long products stay there.
+static_assert(kStageShortK == kFragK, "routes and kernel disagree");
 constexpr int kShortWaves = 4;
 constexpr int kShortRing = 4;
 constexpr int kShortFrags = 16;
@@ -292,54 +292,7 @@ __global__ __launch_bounds__(256) void k_add_partials(ShortGemm g, uint32_t rows
        (((hi >> 16) % m) << 24);
 }
 
-int stages_of(int64_t k) { return (int)((k + kFragK - 1) / kFragK); }
-
-// Moduli a block runs one after another. A block of a few stages spends most
-// of its time before its first stage lands and in its epilogue; with several
-// moduli the next one's copies run under both. GEMM stage, one modulus a
-// block / as chosen: 568 / 514 us at 6000 x 6000 x 384, 342 / 287 at 6000 x
-// 6000 x 100, 196 / 177 at 4096 x 4096 x 256; from k = 1024 on the longer
-// control code costs more (478 / 491 at 4096 x 4096 x 1024), and below about
-// seven rounds of blocks the lost balance does (72.5 / 77.7 for ten moduli at
-// 3000 x 3000 x 300, in 5.6 rounds of two moduli).
-int moduli_per_block(int64_t blocks, int nst, int nmod) {
-  if (nst > 8) return 1;
-  const int64_t most = std::max<int64_t>(1, std::min<int64_t>(6, blocks / 3500));
-  const int groups = (int)((nmod + most - 1) / most);
-  return (nmod + groups - 1) / groups;
-}
-
 }  // namespace
-
-// Estimated time in us of the blocks cut into ns ranges each. 512 blocks run
-// at a time, two a CU; a stage takes 0.47 us there, 0.27 us where the last
-// round leaves every block its own CU; 2.5 us around a block's stages; the
-// second launch 4.5 us and the partial residues' traffic. Measured (GEMM
-// stage, one range / the ranges this chooses): 128 x 128 x 8192, 19 moduli,
-// 38.5 / 18.2 us; 128 x 128 x 2048 15.4 / 13.3; 300 x 300 x 20000 112 / 87;
-// 7 x 5 x 50000 202 / 55; 500 x 400 x 60000 615 / 311 (513 with 256 x 128
-// tiles); no case of 64 .. 1024 a side slower.
-static double short_gemm_us(int64_t blocks, int nst, int ns, double residues) {
-  const int64_t total = blocks * ns, rounds = total / 512, rest = total % 512;
-  const double stages = (double)((nst + ns - 1) / ns);
-  double t = (double)rounds * (stages * 0.47 + 2.5);
-  if (rest > 0) t += stages * (rest <= 256 ? 0.27 : 0.47) + 2.5;
-  if (ns > 1) t += 4.5 + 0.3 * ns + (double)(ns - 1) * residues * 2.0 / 4e6;
-  return t;
-}
-
-int short_gemm_split(int64_t m, int64_t n, int64_t k, int nmod, int nprod) {
-  const int64_t blocks = ((m + kShortTile - 1) / kShortTile) * ((n + kShortTile - 1) / kShortTile) *
-                         nmod * nprod;
-  const int nst = stages_of(k);
-  if (blocks == 0 || blocks > 1024) return 1;   // two rounds and more: nothing to gain
-  const double residues = (double)(m * n) * nmod * nprod;
-  int best = 1;
-  for (int ns = 2; ns <= 16 && nst / ns >= 8; ++ns)
-    if (short_gemm_us(blocks, nst, ns, residues) < short_gemm_us(blocks, nst, best, residues))
-      best = ns;
-  return best;
-}
 
 hipError_t launch_gemm_short(hipStream_t stream, const ShortGemm& g) {
   const int64_t tiles_m = (g.m + kShortTile - 1) / kShortTile;

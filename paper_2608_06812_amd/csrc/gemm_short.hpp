@@ -9,8 +9,6 @@
 
 namespace ozfp4 {
 
-constexpr int kShortTile = 128;   // lines of A and of B per block
-
 // The residues of nprod products of limb planes for the first nmod two-limb
 // moduli l of mc, in one launch. Product q multiplies the planes 2l, 2l + 1
 // at pa + (q / 2) term_a and pb + (q % 2) term_b (one product: q = 0; the
@@ -33,9 +31,6 @@ struct ShortGemm {
   int nmod, nprod, nsplit;
   const ModConst* mc;
 };
-
-// Ranges of k for a product of this size (1: not split).
-int short_gemm_split(int64_t m, int64_t n, int64_t k, int nmod, int nprod);
 
 hipError_t launch_gemm_short(hipStream_t stream, const ShortGemm& g);
 

@@ -6,6 +6,7 @@
 #include "device_common.hpp"
 #include "igemm.hpp"
 #include "limb3_short.hpp"
+#include "routes.hpp"
 
 namespace ozfp4 {
 
@@ -221,21 +222,6 @@ __global__ __launch_bounds__(256) void k_add_partials_s8(ShortS8 g, uint32_t thr
   g.C[(int64_t)col * g.ldc + row] = (int32_t)sum;
 }
 
-int stages_of(int64_t k) { return (int)((k + kFragK - 1) / kFragK); }
-
-// Estimated time in us of the blocks cut into ns ranges (as for the residue
-// GEMM: 512 blocks at a time, two a CU). GEMM, one 128 x 128 block a tile
-// before / the ranges this chooses: 164 x 152 x 7877 71 / 15 us, 601 x 69 x
-// 4441 45 / 14, 33 x 50 x 200001 1591 / 77.
-double s8_us(int64_t blocks, int nst, int ns, double outputs) {
-  const int64_t total = blocks * ns, rounds = total / 512, rest = total % 512;
-  const double stages = (double)((nst + ns - 1) / ns);
-  double t = (double)rounds * (stages * 0.52 + 2.5);
-  if (rest > 0) t += stages * (rest <= 256 ? 0.30 : 0.52) + 2.5;
-  if (ns > 1) t += 4.5 + (double)ns * outputs * 8.0 / 4e6;
-  return t;
-}
-
 }  // namespace
 
 hipError_t launch_encode_s8(hipStream_t stream, const S8Operand& a, const S8Operand& b,
@@ -247,17 +233,6 @@ hipError_t launch_encode_s8(hipStream_t stream, const S8Operand& a, const S8Oper
   const uint32_t ba = blocks(a), bb = blocks(b);
   hipLaunchKernelGGL(k_encode_s8, dim3(ba + bb), dim3(256), 0, stream, a, b, ba, lut8);
   return hipGetLastError();
-}
-
-int short_s8_split(int64_t m, int64_t n, int64_t k) {
-  const int64_t blocks = ((m + kL3TileM - 1) / kL3TileM) * ((n + kL3TileN - 1) / kL3TileN);
-  const int nst = stages_of(k), least = (int)((k + kS8ShortRange - 1) / kS8ShortRange);
-  if (least > 16) return least;   // the caller's rule sends these to the long GEMM
-  int best = least;
-  if (blocks > 1024) return best;
-  for (int ns = least + 1; ns <= 16 && nst / ns >= 8; ++ns)
-    if (s8_us(blocks, nst, ns, (double)(m * n)) < s8_us(blocks, nst, best, (double)(m * n))) best = ns;
-  return best;
 }
 
 hipError_t launch_gemm_s8_short(hipStream_t stream, const ShortS8& g) {

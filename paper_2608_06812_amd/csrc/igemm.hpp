@@ -23,8 +23,6 @@ struct S8Operand {
 hipError_t launch_encode_s8(hipStream_t stream, const S8Operand& a, const S8Operand& b,
                             const uint16_t* lut8);
 
-constexpr int64_t kS8ShortRange = 40960;         // longest k range of a block
-
 // C = A B (m x n, wrapping int32) from the limb planes, k cut into nsplit
 // ranges; with nsplit > 1 the ranges' sums go to `partial` (nsplit sets of
 // m_pad x n_pad int32) and a second launch adds them into C.
@@ -37,9 +35,6 @@ struct ShortS8 {
   int64_t m, n, k, ldc, m_pad, n_pad;
   int nsplit;
 };
-
-// Ranges of k for a product of this size (at least k / kS8ShortRange).
-int short_s8_split(int64_t m, int64_t n, int64_t k);
 
 hipError_t launch_gemm_s8_short(hipStream_t stream, const ShortS8& g);
 

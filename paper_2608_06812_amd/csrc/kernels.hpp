@@ -6,6 +6,7 @@
 #pragma once
 
 #include "device_common.hpp"
+#include "routes.hpp"
 #include "limb3_sched.hpp"
 
 namespace ozfp4 {
@@ -61,9 +62,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_res(
 // Longer k runs in balanced chunks of at most 640 stages (k = 81920); after
 // each chunk the composed sums are added into wrapping uint32 registers,
 // which is exact modulo 2^32.
-constexpr int kTileS8M = 128;
 constexpr int kChunkS8Stages = 640;
-constexpr int kTileS8N = 128;
 __device__ __forceinline__ constexpr int fragA8(int p, int rb, int kbl) { return ((p * 4 + rb) * 2 + kbl) * kFragBytes; }
 __device__ __forceinline__ constexpr int fragB8(int p, int cb, int kbl) { return (24 + (p * 4 + cb) * 2 + kbl) * kFragBytes; }
 

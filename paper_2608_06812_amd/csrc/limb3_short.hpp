@@ -14,6 +14,7 @@
 #pragma once
 
 #include "device_common.hpp"
+#include "routes.hpp"
 
 namespace ozfp4 {
 
@@ -22,7 +23,6 @@ constexpr int kL3Ring = 4;
 constexpr int kL3Frags = 18;
 constexpr int kL3Stage = kL3Frags * kFragBytes;
 constexpr int kL3Dma = 5;
-constexpr int kL3TileM = 128, kL3TileN = 64;
 
 __device__ __forceinline__ constexpr int fragAl3(int p, int rb) { return (p * 4 + rb) * kFragBytes; }
 __device__ __forceinline__ constexpr int fragBl3(int p, int cb) { return (12 + p * 2 + cb) * kFragBytes; }

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "convert.hpp"
+#include "routes.hpp"
 
 namespace ozfp4 {
 
@@ -21,7 +22,6 @@ hipError_t launch_gemm_ozi(hipStream_t stream, const uint8_t* PA, const uint8_t*
 
 // the same over the 128 x 64 tiles that meet the m x n output, for k at most
 // kOziShortK (ozaki1_short.hip)
-constexpr int64_t kOziShortK = 8192;
 hipError_t launch_gemm_ozi_short(hipStream_t stream, const uint8_t* PA, const uint8_t* PB,
                                  int64_t* H, int64_t plane_a, int64_t plane_b, int64_t kblocks,
                                  int64_t m, int64_t n, int64_t k, int64_t m_pad, int64_t n_pad,

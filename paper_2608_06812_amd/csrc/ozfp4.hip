@@ -17,6 +17,7 @@
 #include "onelimb.hpp"
 #include "ozaki1.hpp"
 #include "sgemm.hpp"
+#include "routes.hpp"
 #include "split.hpp"
 #include "ozfp4.h"
 #include "tables.hpp"
@@ -241,35 +242,7 @@ int check_dgemm_args(int64_t m, int64_t n, int64_t k, const void* A, const void*
   return OZFP4_OK;
 }
 
-// Which residue GEMM: the 256 x 128 tile's block has a CU to itself and pays
-// about 7 us around its stages, the 128 x 128 tile (gemm_short.hip) overlaps
-// them with a second block but moves a third more operand bytes. GEMM stage,
-// us, 256 x 128 against 128 x 128, 18 moduli: 63 / 42 at 1024^3, 916 / 571 at
-// 6000 x 6000 x 384, 2328 / 1966 at 6000 x 6000 x 2048, 1885 / 1759 at 4096^3,
-// 29833 / 27431 at 16384 x 16384 x 4096, 13839 / 13820 and 13792 / 13427 at
-// 8192^3, 6690 / 6699 at 4096 x 4096 x 16384, 107793 / 113244 at 16384^3: the
-// line lies at k = 6144. Under four blocks per CU the smaller tile also
-// leaves fewer CUs idle (69 / 39 at 128 x 128 x 8192).
-bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
-  const int64_t blocks = ((m + kTileM - 1) / kTileM) * ((n + kTileN - 1) / kTileN) * nmod;
-  return k <= 6144 || blocks < 1024;
-}
-
-// Which INT8 GEMM: 128 x 128 tiles, one block a CU (k_gemm_s8), or 128 x 64
-// tiles, two blocks a CU and half again as many operand bytes per MFMA
-// (igemm.hip). GEMM, us, in that order: 17.5 / 14.2 at 1000^3, 79 / 73 at
-// 6000 x 6000 x 384, 70 / 68 at 4096 x 4096 x 1024, 461 / 462 at 8192 x 8192
-// x 2048, 220 / 227 at 4096^3, 1661 / 1721 at 8192^3: the line lies at k =
-// 1024. Beyond it the smaller tile, with k ranges, wins where the larger
-// leaves more than 15 % of its rounds' CUs idle (72 / 15 at 164 x 152 x 7877,
-// 816 / 99 at 500 x 500 x 100000; 2048^3, one full round, 35.1 / 35.5).
-bool use_short_s8(int64_t m, int64_t n, int64_t k) {
-  if (k <= 1024) return true;
-  if ((k + kS8ShortRange - 1) / kS8ShortRange > 16) return false;
-  const int64_t blocks = ((m + kTileS8M - 1) / kTileS8M) * ((n + kTileS8N - 1) / kTileS8N);
-  const int64_t slots = (blocks + 255) / 256 * 256;
-  return blocks * 100 < slots * 85;
-}
+static_assert(kLongTileM == kTileM && kLongTileN == kTileN, "routes and kernel disagree");
 
 // Sets nsplit and off_x of a plan whose other fields are set; total_x is
 // total plus the partial residues of the k ranges.
@@ -633,16 +606,6 @@ void make_ozi_plan(int64_t m, int64_t n, int64_t k, int p, OziPlan* o) {
   o->off_pb = off;     off = align256(off + (size_t)o->plane_b * o->nplanes);
   o->off_h = off;      off = align256(off + sizeof(int64_t) * (size_t)o->m_pad * o->n_pad * o->nh);
   o->total = off;
-}
-
-// Which scheme-I GEMM: 128 x 128 units, one a CU, or 128 x 64 units, two a CU
-// (ozaki1_short.hip). GEMM, us, in that order, 15 limbs: 25.6 / 9.5 at 64^3,
-// 108 / 102 at 1024^3, 224 / 211 at 2048 x 2048 x 512, 1465 / 1480 at 4096 x
-// 4096 x 1024, 690 / 697 at 2048^3: short k, or under four units a CU (325 /
-// 202 at 100 x 90 x 8000).
-bool use_short_ozi(int64_t m, int64_t n, int64_t k, int nh) {
-  const int64_t units = ((m + 127) / 128) * ((n + 127) / 128) * nh;
-  return k <= 768 || (k <= kOziShortK && units < 1024);
 }
 
 // Stages, stopping after `last`: 0 scale, 1 encode A, 2 encode B, 3 limb
