@@ -168,11 +168,12 @@ def test_dgemm_phi0_is_correctly_rounded(gpu_lib):
 
 
 def test_residues_adversarial_exactness_at_max_k(gpu_lib):
-    """FP32 accumulators at the exactness limit (k = 131072): every limb of
-    modulus 169 is +8 (residue 112 splits as (8, 8)), so the cross-term
-    accumulator reaches 2^22 in units of the stored values, and the last k
-    adds products of limbs 1 x 1 (a quarter) that an inexact accumulation
-    would drop. Residues of every modulus must still equal the oracle's."""
+    """The largest k (131072) of a product of few tiles, whose short GEMM cuts
+    k into ranges and adds their residues: every limb of modulus 169 is +8
+    (residue 112 splits as (8, 8)), and the last k adds products of limbs
+    1 x 1 (a quarter). Residues of every modulus must equal the oracle's. The
+    same k in one accumulation, at the FP32 limit, is
+    test_gpu_exactness_limits.py's."""
     k = 131072
     m = n = 64
     assert o.two_limb_split(112, 169) == (8, 8)

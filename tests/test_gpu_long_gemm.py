@@ -33,8 +33,10 @@ def _want_residues(A, B, k, L):
         yield q, torch.remainder(torch.round(ra @ rb).to(torch.int64), q).to(torch.uint8)
 
 
-@pytest.mark.parametrize("m,n,k,L", [(1024, 2048, 6145, 18), (1100, 1900, 6272, 16),
-                                     (8000, 2050, 6200, 3)])
+CASES = [(1024, 2048, 6145, 18), (1100, 1900, 6272, 16), (8000, 2050, 6200, 3)]
+
+
+@pytest.mark.parametrize("m,n,k,L", CASES)
 def test_residues_of_long_products(gpu_lib, m, n, k, L):
     import torch
     A, B = dgemm_inputs(m, n, k, 0.5, SEED + m)

@@ -2,11 +2,12 @@
 64-wide stages through a 4-slot ring): every residue against (A~ B~) mod m
 from the oracle's converted integers, exactly. The sizes sit at the edges of
 the ring's fill (1 to 6 stages), of the tile (127 to 129 lines) and of the
-residue composition's ranges of k (1280 / 1281 and 17472 / 17473, where the
-sums of 4 (acc0 + 13 acc1 + 169 acc2) and of 4 (acc1 + 13 acc2) reach 2^24
-at most). Constant operands drive the sums towards those bounds: every
-product of a modulus then has the same sign and limbs. Long inner dimensions
-over few tiles run in several k ranges."""
+residue composition's first border (1280 / 1281 k in one range). Constant
+operands keep the sums from cancelling: every product of a modulus then has
+the same sign and limbs. Long inner dimensions over few tiles run in several
+k ranges, whose lengths stay below the composition's other borders;
+test_gpu_exactness_limits.py takes those in one range, with the largest
+limbs."""
 
 import numpy as np
 import pytest
@@ -32,14 +33,21 @@ CASES = [
     (96, 80, 1280, 18, "constant"),
     (96, 80, 1281, 18, "constant"),
     (200, 140, 1337, 27, "random"),
-    (64, 64, 17472, 18, "constant"),
-    (64, 64, 17473, 18, "constant"),
-    (40, 150, 70000, 19, "constant"),
-    # k cut into ranges whose residues are added modulo m
     (129, 257, 2049, 27, "random"),
     (300, 290, 3000, 18, "constant"),
     (500, 400, 9000, 16, "random"),
     (1030, 900, 700, 18, "random"),
+]
+
+# k cut into ranges whose residues are added modulo m, and how many
+RANGES = [
+    (129, 257, 3000, 18, "random", 2),
+    (300, 290, 9000, 18, "constant", 3),
+    (100, 129, 2049, 18, "random", 4),
+    (500, 400, 20000, 18, "random", 5),
+    (64, 64, 17472, 18, "constant", 13),
+    (64, 64, 17473, 18, "constant", 14),
+    (40, 150, 70000, 19, "constant", 13),
 ]
 
 # outputs of enough tiles that a block runs several moduli (k up to 512):
@@ -58,7 +66,7 @@ def _inputs(m, n, k, kind):
     return A, B
 
 
-@pytest.mark.parametrize("m,n,k,L,kind", CASES)
+@pytest.mark.parametrize("m,n,k,L,kind", CASES + [c[:-1] for c in RANGES])
 def test_residues_of_short_products(gpu_lib, m, n, k, L, kind):
     A, B = _inputs(m, n, k, kind)
     moduli = o.select_moduli(L)

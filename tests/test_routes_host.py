@@ -4,6 +4,9 @@ route still take it."""
 
 import random
 
+import test_gpu_exactness_limits as limits
+import test_gpu_long_gemm as long_gemm
+import test_gpu_short_gemm as short_gemm
 from route_util import longest_range, routes
 
 
@@ -31,3 +34,20 @@ def test_ranges_stay_within_their_bounds():
     sizes = _sizes(rng, 4000, 17)
     for (m, n, k), (kernel,) in zip(sizes, routes([("ozi", *s, 9) for s in sizes])):
         assert kernel == "long" or k <= 8192      # 960 k < 2^23
+
+
+def test_limit_cases_reach_their_kernel_in_one_range():
+    want = [kernel for *_, kernel in limits.RESIDUES]
+    got = routes([("res", m, n, k, L, 1) for m, n, k, L, _ in limits.RESIDUES])
+    assert got == [(kernel, 1, 1) for kernel in want]
+    assert routes([("s8", m, n, k) for m, n, k, _ in limits.INT8]) == \
+        [(kernel, 1) for *_, kernel in limits.INT8]
+    assert routes([("ozi", *limits.OZI, 9)]) == [("short",)]
+
+
+def test_cases_of_the_residue_gemms_take_their_route():
+    ask = lambda cases: routes([("res", *c[:4], 1) for c in cases])
+    assert ask(short_gemm.RANGES) == [("short", c[5], 1) for c in short_gemm.RANGES]
+    assert {r[:2] for r in ask(short_gemm.CASES)} == {("short", 1)}
+    assert all(kernel == "short" and group > 1 for kernel, _, group in ask(short_gemm.GROUPED))
+    assert {r[0] for r in ask(long_gemm.CASES)} == {"long"}
