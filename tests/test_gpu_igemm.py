@@ -25,9 +25,9 @@ def test_igemm_s8_bit_exact(gpu_lib, m, n, k):
 
 
 def test_igemm_s8_extremes_at_the_fp32_limit(gpu_lib):
-    """All -128 (the largest limb products) at k = 87381, the FP32-exactness
-    limit of one grouped accumulation (the library runs it as two chunks);
-    plus mixed signs."""
+    """All -128 (the largest values) at k = 87381, the FP32-exactness limit of
+    one grouped accumulation, which the short GEMM cuts into ranges well below
+    it; plus mixed signs."""
     k = 87381
     A = np.full((128, k), -128, dtype=np.int8)
     B = np.full((k, 64), -128, dtype=np.int8)
@@ -41,9 +41,9 @@ def test_igemm_s8_extremes_at_the_fp32_limit(gpu_lib):
 
 
 def test_igemm_s8_long_k_chunks_and_wraps(gpu_lib):
-    """k = 200000: three accumulation chunks, and with every value -128 the
-    exact products reach 2^31.6, so C must wrap modulo 2^32 like INT32
-    accumulation; mixed signs and a ragged shape around it."""
+    """k = 200000, in ranges of the short GEMM whose sums are added: with every
+    value -128 the exact products reach 2^31.6, so C must wrap modulo 2^32
+    like INT32 accumulation; mixed signs and a ragged shape around it."""
     k = 200000
     A = np.full((70, k), -128, dtype=np.int8)
     B = np.full((k, 40), -128, dtype=np.int8)

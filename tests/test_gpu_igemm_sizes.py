@@ -3,7 +3,9 @@ numpy's integer product modulo 2^32: the encoder's blocks of 128 lines x 64
 k with whole and partial words, leading dimensions that leave rows and
 columns unaligned, the short GEMM's ring fill (1 to 6 stages of 64), tile
 remainders, k ranges (with sums that wrap) and the rule's borders to the long
-GEMM (k = 1024, a full round of tiles, more than 16 ranges)."""
+GEMM (k = 1024, a full round of tiles, more than 16 ranges). The ranges here
+are short of the longest one that is exact, which
+test_gpu_exactness_limits.py takes."""
 
 import numpy as np
 import pytest

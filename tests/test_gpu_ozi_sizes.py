@@ -2,8 +2,9 @@
 one's ring and tiles: partial sums H against the oracle's limbs, multiplied
 exactly in FP64 on the CPU. 1 to 6 stages per pair, one to five limb blocks,
 tile remainders, tile counts that 8 divides and does not, k at the border of
-the short GEMM's exactness (8192) with operands whose sums do not cancel, and
-the long GEMM just beyond."""
+the short GEMM's rule (8192) with operands whose sums do not cancel, and the
+long GEMM just beyond. (The largest limbs at 8192 are
+test_gpu_exactness_limits.py's.)"""
 
 import numpy as np
 import pytest
@@ -24,10 +25,19 @@ CASES = [
 ]
 
 
+def _blocks(Xi, p):
+    """Values of the blocks of three greedy limbs."""
+    limbs = o.ozi_limbs(Xi, p)
+    limbs += [np.zeros_like(limbs[0])] * (-p % 3)
+    return [(limbs[i] + 13 * limbs[i + 1] + 169 * limbs[i + 2]).astype(np.float64)
+            for i in range(0, len(limbs), 3)]
+
+
 @pytest.mark.parametrize("m,n,k,p,same", CASES)
 def test_dgemm_ozi_at_the_edges(gpu_lib, m, n, k, p, same):
-    """C against the product of the converted integers (exact integers),
-    through the oracle's own final rounding."""
+    """Every partial sum H against the oracle's limbs, and sampled outputs C
+    against the product of the converted integers (exact integers), correctly
+    rounded."""
     if same:   # one value per line: no cancellation over k
         rng = np.random.default_rng(SEED + k)
         A = np.repeat(1.0 + rng.random((m, 1)), k, axis=1)
@@ -39,6 +49,15 @@ def test_dgemm_ozi_at_the_edges(gpu_lib, m, n, k, p, same):
     cap, _, _ = gpu_lib.ozfp4_ozi_config(p)
     s = np.asarray(o.shift_exponents(A, axis=1, c=cap), dtype=np.int64)
     t = np.asarray(o.shift_exponents(B, axis=0, c=cap), dtype=np.int64)
+    H = to_np(gpu_lib.ozi_partials(dev_cm(A), dev_cm(B), p))
+    # block values below 8 (1 + 13 + 169): sums below 2^53, exact in FP64
+    D = _blocks(o.to_integers(A, s, axis=1), p)
+    E = _blocks(o.to_integers(B, t, axis=0), p)
+    nblk = len(D)
+    assert H.shape[0] == 2 * nblk - 1 and nblk * 1464.0 ** 2 * k < 2.0 ** 53
+    for h in range(2 * nblk - 1):
+        want = sum(D[I] @ E[h - I] for I in range(nblk) if 0 <= h - I < nblk)
+        assert np.array_equal(H[h].T, want.astype(np.int64)), h
     rows = sorted({0, m // 2, m - 1})
     cols = sorted({0, 31 % n, n // 2, n - 1})
     Ai = o.to_integers(A[rows], s[rows], axis=1)
