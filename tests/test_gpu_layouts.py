@@ -1,9 +1,9 @@
-"""GPU parity of every product over the storage orders that the torch helpers
-accept: row-major operands are read in place, every other layout through a
-column-major copy, and each gives the bits of the same matrix in column-major
-order. Odd sizes and leading dimensions leave lines unaligned; a single row,
-a single column, step slices, expanded rows and transposed views are among
-the forms."""
+"""GPU parity of every product, the opt-in modes of the FP64 one included, over
+the storage orders that the torch helpers accept: row-major operands are read
+in place, every other layout through a column-major copy, and each gives the
+bits of the same matrix in column-major order. Odd sizes and leading
+dimensions leave lines unaligned; a single row, a single column, step slices,
+expanded rows and transposed views are among the forms."""
 
 import numpy as np
 import pytest
@@ -14,6 +14,18 @@ pytestmark = pytest.mark.gpu
 
 SEED = 20261208
 
+
+def _with(setter, on, off, call):
+    """call with an opt-in mode of the library set around it."""
+    def run(g, A, B):
+        getattr(g, setter)(on)
+        try:
+            return call(g, A, B)
+        finally:
+            getattr(g, setter)(off)
+    return run
+
+
 PRODUCTS = {
     "dgemm": ("float64", lambda g, A, B: g.dgemm(A, B, 18)),
     "noalloc": ("float64", lambda g, A, B: g.dgemm_noalloc(
@@ -22,6 +34,10 @@ PRODUCTS = {
     "ozi": ("float64", lambda g, A, B: g.dgemm_ozi(A, B, 15)),
     "sgemm": ("float32", lambda g, A, B: g.sgemm(A, B)),
     "igemm": ("int8", lambda g, A, B: g.igemm_s8(A, B)),
+    "wide": ("float64", _with("ozfp4_set_max_capacity", 63, 53, lambda g, A, B: g.dgemm(A, B, 23))),
+    "heads": ("float64", _with("ozfp4_set_one_limb_moduli", 5, 0, lambda g, A, B: g.dgemm(A, B, 21))),
+    "karatsuba": ("float64", _with("ozfp4_set_karatsuba", True, False,
+                                   lambda g, A, B: g.dgemm(A, B, 18))),
 }
 
 
