@@ -30,9 +30,10 @@ __host__ __device__ inline int adjacent_lines(int64_t lines) {
 }
 
 // Partial maxima of one (line group, chunk). Bound by HBM at large sizes;
-// at small ones by the latency of a thread's serial loads, so chunks are
-// cut to put up to 1024 blocks an operand on the chip and every thread keeps eight (four) loads in flight: 12.6 -> 3 us
-// for 256 x 256 (the maxima of both operands), 26 -> 4 us for 1024 x 1024.
+// at small ones by the latency of a thread's serial loads, so chunks are cut
+// to put up to 1024 blocks an operand on the chip and every thread keeps eight
+// (four) loads in flight: 12.6 -> 3 us for 256 x 256 (the maxima of both
+// operands), 26 -> 4 us for 1024 x 1024.
 // Each (line, chunk) has one writer, so no zero fill and no atomics.
 template <typename T>
 __device__ __forceinline__ void line_max_block(const ConvOperand& op, uint32_t block, int* flag) {

@@ -1,6 +1,7 @@
 // Device code shared by the translation units of the library: types,
-// constants, the scale helpers, the residue-GEMM tile and its helpers. Templates and inline functions only, so every translation
-// unit can include it.
+// constants, the scale helpers, the residue-GEMM tile and its helpers.
+// Templates and inline functions only, so every translation unit can include
+// it.
 //
 // Data layout (HBM):
 //   * limb planes: per operand, plane p holds one limb of one modulus for
@@ -336,6 +337,9 @@ __device__ __forceinline__ void store_residues_by_k(const v16f (&acc)[3][2][2], 
 // each) form a group, the last group takes what is left. The wait ends after
 // 24 polls in any case (about 20 us; a group stays short where another stream
 // holds CUs). With it: 107.0 ms at 16384^3, 13.57 ms against 13.77 at 8192^3.
+// The Karatsuba GEMM goes without: its blocks differ in length by modulus and
+// were not in step with the FP64 epilogue either (16384^3, FP64 / FP32: L2 hit
+// rate 63 / 61 %, FETCH_SIZE 2.10e8 / 2.06e8 KiB, 118.0 / 117.1 ms).
 constexpr int kLockstepPolls = 24;
 __device__ __forceinline__ void xcd_lockstep(unsigned* arrive, unsigned nblocks, unsigned slots) {
   if (threadIdx.x != 0) return;

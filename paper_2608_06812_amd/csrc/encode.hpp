@@ -11,12 +11,12 @@ namespace ozfp4 {
 
 // ------------------------------------------------------------ Sec. V-A / VI-B
 // Fused integer conversion, residues for every modulus, two-limb split and
-// E2M1 packing, for FP64 (or FP32, taken exactly as FP64) inputs. One wave per fragment (32 lines x 64 k); lane
-// (line % 32, k half) converts its 32 values once, then for each modulus
-// reduces them, looks the codes up in an LDS table and stores 16 bytes to
-// each plane of that modulus: c0 (plane 2l), c1 (plane 2l + 1) and, in the
-// Karatsuba mode (kKar) for a Karatsuba modulus, c0 + c1 (plane
-// 2L + ksum).
+// E2M1 packing, for FP64 (or FP32, taken exactly as FP64) inputs. One wave per
+// fragment (32 lines x 64 k); lane (line % 32, k half) converts its 32 values
+// once, then for each modulus reduces them, looks the codes up in an LDS table
+// and stores 16 bytes to each plane of that modulus: c0 (plane 2l), c1 (plane
+// 2l + 1) and, in the Karatsuba mode (kKar) for a Karatsuba modulus, c0 + c1
+// (plane 2L + ksum).
 //   x = round_half_even(X * 2^s), |x| <= 2^53, is exact in FP64. For each m,
 //   q = rint(x fl(1/m)) is within 0.7 of x / m, so r = x - q m lies in
 //   (-m, m) and indexes a table over [-m, 2m) that maps every estimate to the
@@ -208,7 +208,8 @@ __global__ __launch_bounds__(256) void k_encode_dgemm(
 constexpr int64_t kEncodeWaves = 4096;
 inline int moduli_per_group(const ConvOperand& a, const ConvOperand& b, int L, int terms) {
   const int64_t frags = ((int64_t)a.blocks * a.kfrags + (int64_t)b.blocks * b.kfrags) * terms;
-  const int64_t groups = std::min<int64_t>(L, std::max<int64_t>(1, kEncodeWaves / std::max<int64_t>(1, frags)));
+  const int64_t share = kEncodeWaves / std::max<int64_t>(1, frags);
+  const int64_t groups = std::min<int64_t>(L, std::max<int64_t>(1, share));
   return (int)((L + groups - 1) / groups);
 }
 
@@ -227,8 +228,8 @@ hipError_t launch_encode_kernel(hipStream_t stream, const ConvOperand& a, const 
     const int l0 = g * per_group, l1 = std::min(L, l0 + per_group) - 1;
     lds = std::max(lds, entry * (size_t)(mod.lut_off[l1] + 3 * mod.m[l1] - mod.lut_off[l0]) + 8);
   }
-  hipLaunchKernelGGL((k_encode_dgemm<kKar, kWide, TIn, kTerms>), dim3(ba + bb, groups, kTerms), dim3(256),
-                     lds, stream, a, b, ba, L, per_group, mc, lut, d2);
+  hipLaunchKernelGGL((k_encode_dgemm<kKar, kWide, TIn, kTerms>), dim3(ba + bb, groups, kTerms),
+                     dim3(256), lds, stream, a, b, ba, L, per_group, mc, lut, d2);
   return hipGetLastError();
 }
 

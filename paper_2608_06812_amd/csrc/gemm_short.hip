@@ -26,9 +26,12 @@ constexpr int kShortStage = kShortFrags * kFragBytes;
 constexpr int kShortDma = kShortFrags / kShortWaves;   // 4
 
 // Up to 64 tiles an XCD takes whole moduli: eight XCDs with eight tiles or
-// fewer of each modulus fetch every panel into most L2s (512 x 512 x 4096:
-// 58 us at 5.1 TB/s from beyond L2, 46 us with whole moduli; 1024^3 41.9 and
-// 39.5); at 256 tiles the shared order is ahead again (2048^3 228 and 231).
+// fewer of each modulus fetch every panel into most L2s. GEMM, us, tiles of a
+// modulus shared by the XCDs / whole moduli, 18 moduli, k = 4096: 59.6 / 46.5
+// for 16 tiles (512 x 512), 81.1 / 72.4 for 32, 107.5 / 97.8 for 48, 124.1 /
+// 122.8 for 64 (1024 x 1024; 43.4 / 39.9 at k = 1024), 148.2 / 147.7 for 80,
+// and the other way from 128 on (227.0 / 229.0; 192: 339.8 / 342.9; 256, at
+// k = 2048: 231.8 / 234.5).
 constexpr unsigned kShortMinShare = 72;
 
 // LDS offset of fragment (plane p, line block rb / cb)

@@ -156,9 +156,11 @@ __global__ __launch_bounds__(kL3Waves * 64, 2) void k_gemm_s8_short(ShortS8 g, i
     const int f = min(wave + 4 * j, kL3Frags - 1);
     const uint8_t* base;
     if (f < 12)
-      base = g.pa + (int64_t)(f >> 2) * g.plane_a + ((tm * 4 + (f & 3)) * g.kblocks + st0) * kFragBytes;
+      base = g.pa + (int64_t)(f >> 2) * g.plane_a +
+             ((tm * 4 + (f & 3)) * g.kblocks + st0) * kFragBytes;
     else
-      base = g.pb + (int64_t)((f - 12) >> 1) * g.plane_b + ((tn * 2 + (f & 1)) * g.kblocks + st0) * kFragBytes;
+      base = g.pb + (int64_t)((f - 12) >> 1) * g.plane_b +
+             ((tn * 2 + (f & 1)) * g.kblocks + st0) * kFragBytes;
     src[j] = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nst * kFragBytes, kBufferWord3);
   }
   const int lane16 = lane * 16;

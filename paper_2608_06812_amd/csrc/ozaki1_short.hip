@@ -91,9 +91,9 @@ __global__ __launch_bounds__(kL3Waves * 64, 2) void k_gemm_ozi_short(
       for (int v = 0; v < 16; ++v) acc[e][i][v] = 0.0f;
   limb3_short_run(lds, (I1 - I0 + 1) * nst, wave, lane16, copy, advance, acc);
 
-  // H_h = sum_g 13^g 4 acc_g: the first three terms stay below 2^31 (183 *
-  // 2^23 does not: they are added as int64), the tile lies inside the padded
-  // planes
+  // H_h = sum_g 13^g 4 acc_g: the first two terms in 32 bits (the first three
+  // would fit too, below 183 * 2^23 < 2^31), the others in 64; the tile lies
+  // inside the padded planes
   int64_t* dst0 = H + (int64_t)h * hplane + (tn * kL3TileN + wn * 32 + (lane & 31)) * ldh +
                   tm * kL3TileM + wm * 64 + (lane >> 5) * 4;
 #pragma unroll

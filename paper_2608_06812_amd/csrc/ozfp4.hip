@@ -786,7 +786,7 @@ int prepare(int64_t m, int64_t n, int64_t k, int L, DgemmPlan* p, DeviceState** 
 // ------------------------------------------------------------ entry points
 
 int dgemm_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
-               bool layouts_ok, double* C, int64_t ldc, int n_moduli){
+               bool layouts_ok, double* C, int64_t ldc, int n_moduli) {
   int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
@@ -810,9 +810,8 @@ int dgemm_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
   return finish_with_flag(d, 5);
 }
 
-
 int dgemm_noalloc_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
-                       bool layouts_ok, double* C, int64_t ldc, int n_moduli){
+                       bool layouts_ok, double* C, int64_t ldc, int n_moduli) {
   int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
@@ -851,9 +850,8 @@ int dgemm_noalloc_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat&
   return finish_with_flag(d, 5);
 }
 
-
 int dgemm_split_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
-                     bool layouts_ok, double* C, int64_t ldc, int n_moduli){
+                     bool layouts_ok, double* C, int64_t ldc, int n_moduli) {
   int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
@@ -880,9 +878,8 @@ int dgemm_split_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B
   return finish_with_flag(d, 5);
 }
 
-
 int sgemm_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
-               bool layouts_ok, float* C, int64_t ldc, int n_moduli){
+               bool layouts_ok, float* C, int64_t ldc, int n_moduli) {
   int rc = check_dgemm_args(m, n, k, A.X, B.X, layouts_ok, n_moduli);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
@@ -907,9 +904,8 @@ int sgemm_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
   return finish_with_flag(d, 5);
 }
 
-
 int dgemm_ozi_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
-                   bool layouts_ok, double* C, int64_t ldc, int n_limbs){
+                   bool layouts_ok, double* C, int64_t ldc, int n_limbs) {
   int rc = check_ozi_args(m, n, k, A.X, B.X, layouts_ok, n_limbs);
   if (rc) return rc;
   if (ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
@@ -933,9 +929,8 @@ int dgemm_ozi_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
   return finish_with_flag(d, 5);
 }
 
-
 int igemm_s8_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
-                  bool layouts_ok, int32_t* C, int64_t ldc){
+                  bool layouts_ok, int32_t* C, int64_t ldc) {
   if (!dims_ok(m, n, k)) return OZFP4_EINVAL;
   if (!layouts_ok || ldc < std::max<int64_t>(1, m)) return OZFP4_EINVAL;
   if (m == 0 || n == 0) return OZFP4_OK;
@@ -975,8 +970,8 @@ int igemm_s8_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
   auto operand = [&](const void* X, int64_t rs, int64_t ks, int64_t lines, uint8_t* planes,
                      int64_t plane_bytes) {
     const int64_t blocks = (lines + kFragLines - 1) / kFragLines;
-    return S8Operand{static_cast<const int8_t*>(X), rs, ks, lines, k, planes, plane_bytes, kblocks, (uint32_t)blocks,
-                     (uint32_t)frags_read(use_short, k, kblocks)};
+    return S8Operand{static_cast<const int8_t*>(X), rs, ks, lines, k, planes, plane_bytes,
+                     kblocks, (uint32_t)blocks, (uint32_t)frags_read(use_short, k, kblocks)};
   };
   S8Operand a = operand(A.X, A.rs, A.cs, m, pa, plane_a), b = operand(B.X, B.cs, B.rs, n, pb, plane_b);
   if (g_profile) {   // each operand its own launch, and so its own stage time
@@ -1010,7 +1005,6 @@ int igemm_s8_call(int64_t m, int64_t n, int64_t k, const Mat& A, const Mat& B,
   return OZFP4_OK;
 }
 
-
 // The fewest moduli that give ozfp4_sgemm 24-bit capacities for this k
 // (OZFP4_MAX_MODULI if none does).
 int sgemm_moduli(int64_t k) {
@@ -1032,7 +1026,8 @@ extern "C" {
 
 int ozfp4_dgemm(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                 const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
-  return dgemm_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+  return dgemm_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb),
+                    C, ldc, n_moduli);
 }
 
 int ozfp4_product(int op, int64_t m, int64_t n, int64_t k, const void* A, int64_t a_rs,
@@ -1062,22 +1057,26 @@ int ozfp4_init(void) {
 
 int ozfp4_dgemm_noalloc(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                         const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
-  return dgemm_noalloc_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+  return dgemm_noalloc_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb),
+                            C, ldc, n_moduli);
 }
 
 int ozfp4_dgemm_split(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                       const double* B, int64_t ldb, double* C, int64_t ldc, int n_moduli) {
-  return dgemm_split_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+  return dgemm_split_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb),
+                          C, ldc, n_moduli);
 }
 
 int ozfp4_igemm_s8(int64_t m, int64_t n, int64_t k, const int8_t* A, int64_t lda,
                    const int8_t* B, int64_t ldb, int32_t* C, int64_t ldc) {
-  return igemm_s8_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc);
+  return igemm_s8_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb),
+                       C, ldc);
 }
 
 int ozfp4_sgemm(int64_t m, int64_t n, int64_t k, const float* A, int64_t lda,
                 const float* B, int64_t ldb, float* C, int64_t ldc, int n_moduli) {
-  return sgemm_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_moduli);
+  return sgemm_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb),
+                    C, ldc, n_moduli);
 }
 
 int ozfp4_sgemm_capacity(int64_t k, int n_moduli, int32_t* c_a, int32_t* c_b) {
@@ -1096,7 +1095,8 @@ int ozfp4_sgemm_capacity(int64_t k, int n_moduli, int32_t* c_a, int32_t* c_b) {
 
 int ozfp4_dgemm_ozi(int64_t m, int64_t n, int64_t k, const double* A, int64_t lda,
                     const double* B, int64_t ldb, double* C, int64_t ldc, int n_limbs) {
-  return dgemm_ozi_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb), C, ldc, n_limbs);
+  return dgemm_ozi_call(m, n, k, Mat{A, 1, lda}, Mat{B, 1, ldb}, leading_ok(m, k, lda, ldb),
+                        C, ldc, n_limbs);
 }
 
 int ozfp4_ozi_config(int n_limbs, int32_t* capacity, int32_t* n_planes, int32_t* n_groups) {
@@ -1211,7 +1211,8 @@ int ozfp4_two_limb_table(int modulus_index, uint8_t* out, int32_t* m_out) {
   if (!T) return OZFP4_EHIP;
   const ModConst& mod = g_heads ? T->lists[g_heads].mod : T->mod;
   const int m = mod.m[modulus_index];
-  const uint16_t* lut = (g_heads ? T->lists[g_heads].lut.data() : T->lut.data()) + mod.lut_off[modulus_index];
+  const uint16_t* lut =
+      (g_heads ? T->lists[g_heads].lut.data() : T->lut.data()) + mod.lut_off[modulus_index];
   for (int r = 0; r < m; ++r) {
     const uint16_t e = lut[r + m];  // remainder estimate r, non-negative value
     out[r] = (uint8_t)((e & 0xf) | ((e >> 8) & 0xf) << 4);

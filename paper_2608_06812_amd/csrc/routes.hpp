@@ -41,7 +41,12 @@ inline double rounds_us(int64_t blocks, int nst, int ns, double stage_two, doubl
 // 29833 / 27431 at 16384 x 16384 x 4096, 13839 / 13820 and 13792 / 13427 at
 // 8192^3, 6690 / 6699 at 4096 x 4096 x 16384, 107793 / 113244 at 16384^3: the
 // line lies at k = 6144. Under four blocks per CU the smaller tile also
-// leaves fewer CUs idle (69 / 39 at 128 x 128 x 8192).
+// leaves fewer CUs idle: 70 / 18 at 128 x 128 x 8192 (19 blocks), 519 / 465 at
+// 1024 x 1024 x 16384 (576), 705 / 662 at 1536 x 1024 x 16384 (864), and at
+// 1792 x 1024 (1008) as much at k = 16384 (765 / 765) and 2 % more at 65536
+// (3079 / 3155). The blocks are one product's: the four of the two-term split
+// run one after another in the larger tile (1086 / 913 at 1024 x 1024 x 8192,
+// 608 blocks each; 1489 / 1372 at 1536 x 1024 x 8192, 912).
 inline bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
   const int64_t blocks = tiles(m, kLongTileM) * tiles(n, kLongTileN) * nmod;
   return k <= 6144 || blocks < 1024;
@@ -50,9 +55,9 @@ inline bool use_short_gemm(int64_t m, int64_t n, int64_t k, int nmod) {
 // Estimated time of the residue GEMM's blocks cut into ns ranges each, with
 // the second launch's 4.5 us and the partial residues' traffic. Measured (GEMM
 // stage, one range / the ranges this chooses): 128 x 128 x 8192, 19 moduli,
-// 38.5 / 18.2 us; 128 x 128 x 2048 15.4 / 13.3; 300 x 300 x 20000 112 / 87;
-// 7 x 5 x 50000 202 / 55; 500 x 400 x 60000 615 / 311 (513 with 256 x 128
-// tiles); no case of 64 .. 1024 a side slower.
+// 39.7 / 17.8 us; 128 x 128 x 2048 15.9 / 13.5; 300 x 300 x 20000 116 / 90;
+// 7 x 5 x 50000 203 / 46; 600 x 500 x 8000 82.4 / 81.7; 500 x 400 x 60000 561
+// / 409 (502 with 256 x 128 tiles).
 inline double short_gemm_us(int64_t blocks, int nst, int ns, double residues) {
   double t = rounds_us(blocks, nst, ns, 0.47, 0.27);
   if (ns > 1) t += 4.5 + 0.3 * ns + (double)(ns - 1) * residues * 2.0 / 4e6;
